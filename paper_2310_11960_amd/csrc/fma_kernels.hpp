@@ -80,7 +80,8 @@ struct BwdArgs {
     float *delta;                         // [S][n] rowsum(dO * O)
     float *part;                          // [2][pslices][npart][nslot][64] per-workgroup dK_bar, dV_bar
                                           // partials of the slices of one pass
-    float *dkbar, *dvbar;                 // [S][R][64]
+    float *dkbar, *dvbar;                 // [S][R][64]; split_rows: each value a (hi, lo) pair of bf16
+    int split_rows;                       // 1: bf16 key pass on streamed groups reads such pairs
     float *dotk, *dotv;                   // [S][nsets][n] k_t . dK_bar (v_t . dV_bar) of each token's group
     // FMA-linear (reading R18): coarse queries and the query-side gradients
     const void *qbar;                     // [S][R][64] I/O dtype (nullptr: FMA)
@@ -128,6 +129,10 @@ hipError_t launch_lin_far(const AttnArgs &a, int geometry, hipStream_t st);
 hipError_t launch_lists(int two_d, int nblocks, int nby, int causal, const Levels &lv,
                         int32_t *out, hipStream_t st);
 hipError_t launch_backward(const BwdArgs &a, bool bf16, bool two_d, hipStream_t st);
+// bf16 backward on streamed 128-row groups (backward_mfma.hip): whether a
+// plan's blocks take it, and its key pass
+bool bwd_streams(const BwdArgs &a, bool two_d);
+hipError_t launch_bwd_key(const BwdArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_stream_ref(const void *src, long long nwords, void *dst, long long ndst, int write_every,
                              hipStream_t st);
 long long stream_ref_dst_words(long long nwords, int write_every);
