@@ -23,7 +23,10 @@
 // and the coarsening is linear, so a coarse row's gradient flows back as
 //     dk_j += pi[j - start] dk_bar,   dpi[o] += k_(start+o) . dk_bar.
 //
-// Kernels, in launch order (the forward's coarsening rebuilds K_bar, V_bar):
+// Kernels, in launch order (the forward's coarsening rebuilds K_bar, V_bar).
+// bf16 plans under the joint normalisation with blocks of 32 tokens and more
+// or cells of 8 x 8 and more take bwd_query_mfma, bwd_coarse_mfma and
+// bwd_group_reduce (backward_mfma.hip) for the first two:
 //   bwd_query   a wave per 32 queries (waves of one block share the tiles):
 //               D_i = rowsum(dO * O) of its queries (written for bwd_key); one
 //               pass over the query's tiles for lse and dQ (online rescaling
@@ -942,65 +945,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
     }
 }
 
-// Sums of partial rows, one wave per output row: the terms, numbered in a
-// fixed order, are dealt round-robin to NG groups of 64 / NG lanes (a lane
-// takes eight channels), so NG partial rows are in flight per load.
-// deal_box calls f(dx, dy, k) for the terms of an nx x ny x nk box (k
-// fastest) numbered t0, t0 + 1, ... that fall to group grp, in ascending
-// order; the caller advances t0 by the box's size.
-template <int NG, typename F>
-__device__ inline void deal_box(int nx, int ny, int nk, int grp, int t0, F f)
-{
-    const int nt = nx * ny * nk;
-    int w = (grp - t0) & (NG - 1);   // this group's first term of the box
-    int k = w % nk, dy = (w / nk) % ny, dx = (w / nk) / ny;
-    for (; w < nt; w += NG) {
-        f(dx, dy, k);
-        k += NG;   // NG terms on
-        while (k >= nk) {
-            k -= nk;
-            ++dy;
-        }
-        while (dy >= ny) {
-            dy -= ny;
-            ++dx;
-        }
-    }
-}
-
-// acc[i] += the eight floats at p (16-byte aligned), bounds-checked
-__device__ inline void add8(float acc[8], const float *p, long long idx, long long lim)
-{
-    const uint4 p0 = ld16(p, idx, 4, lim), p1 = ld16(p, idx + 4, 4, lim);
-    acc[0] += __uint_as_float(p0.x);
-    acc[1] += __uint_as_float(p0.y);
-    acc[2] += __uint_as_float(p0.z);
-    acc[3] += __uint_as_float(p0.w);
-    acc[4] += __uint_as_float(p1.x);
-    acc[5] += __uint_as_float(p1.y);
-    acc[6] += __uint_as_float(p1.z);
-    acc[7] += __uint_as_float(p1.w);
-}
-
-// The eight groups' sums (lanes 8 grp + x hold channels 8 x ..): lanes of
-// group 0 end with ((g0 + g1) + (g2 + g3)) + ((g4 + g5) + (g6 + g7)) and
-// store them (split: as (hi, lo) bf16 pairs).
-__device__ inline void store_group_sums(float acc[8], int grp, float *dst, long long o, long long lim, bool split = false)
-{
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float x = acc[i];
-        x += __shfl_xor(x, 8);
-        x += __shfl_xor(x, 16);
-        x += __shfl_xor(x, 32);
-        acc[i] = split ? __uint_as_float(bf16_pair(x)) : x;
-    }
-    if (grp == 0) {
-        st4f(dst, o, lim, acc[0], acc[1], acc[2], acc[3]);
-        st4f(dst, o + 4, lim, acc[4], acc[5], acc[6], acc[7]);
-    }
-}
-
 // One workgroup (one wave) per (tensor, slice, coarse row).  The query
 // groups whose interaction list holds the row lie within 3 groups of it
 // along each axis (the list is the parent's 6-wide window); the first
@@ -1141,23 +1085,6 @@ __device__ inline int slot_of(const BwdArgs &a, int e, int j)
 }
 
 // --------------------------------------------------------------- bwd_reduce
-// The entry j of level group (qx, qy)'s 2D list that names square (u, v)
-// of the same level, or -1: the inverse of list2d_entry (the square's place
-// in the row-major 6x6 window around the parent, skipping the 3x3 block at
-// (1 + (qx & 1), 1 + (qy & 1)); see window_slot), for squares inside the map.
-__device__ inline int list2d_slot_of(int qx, int qy, int u, int v)
-{
-    const int au = u - (2 * (qx >> 1) - 2), av = v - (2 * (qy >> 1) - 2);
-    if (au < 0 || au >= 6 || av < 0 || av >= 6) return -1;
-    const int ox = 1 + (qx & 1), oy = 1 + (qy & 1);
-    if (au < ox) return au * 6 + av;
-    if (au < ox + 3) {
-        if (av >= oy && av < oy + 3) return -1;   // the finer levels' squares
-        return 6 * ox + (au - ox) * 3 + (av < oy ? av : av - 3);
-    }
-    return 6 * ox + 9 + (au - ox - 3) * 6 + av;
-}
-
 template <bool TWO_D>
 __global__ __launch_bounds__(64) void bwd_reduce(BwdArgs a)
 {
@@ -1957,7 +1884,7 @@ hipError_t launch_all(const BwdArgs &a0, hipStream_t st)
     a.npart = a.nblocks * ((cpb + NW - 1) / NW);   // (query block, workgroup) rows per slice
     if (a.pslices <= 0) return hipErrorInvalidValue;
     a.split_rows = BF16 && bwd_streams(a, TWO_D);
-    if ((long long)2 * a.pslices * a.npart * a.nslot * kHeadDim > a.part_elems && a.lv.nlev > 0)
+    if (a.ngrp == 0 && (long long)2 * a.pslices * a.npart * a.nslot * kHeadDim > a.part_elems && a.lv.nlev > 0)
         return hipErrorInvalidValue;
     if (LIN && a.lv.nlev > 0 &&
         ((long long)a.nslice * a.npart * a.lv.nlev * kHeadDim > a.qpart_elems ||
@@ -1969,25 +1896,32 @@ hipError_t launch_all(const BwdArgs &a0, hipStream_t st)
     const int runs = (int)runs_ll;
     hipError_t e = hipSuccess;
     const long long per_slice = (long long)a.nblocks * ((cpb + NW - 1) / NW);   // query-pass workgroups
-    // the query pass and the reduction of its partials, pslices slices at a time
-    for (int s0 = 0; s0 < a.nslice; s0 += a.pslices) {
-        BwdArgs b = a;
-        b.slice0 = s0;
-        const int cnt = a.nslice - s0 < a.pslices ? a.nslice - s0 : a.pslices;
-        hipLaunchKernelGGL((bwd_query<BF16, TWO_D, NW, PL, LIN>), dim3((unsigned)(cnt * per_slice)), dim3(64 * NW), 0,
-                           st, b);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (a.lv.nlev > 0) {
-            // grid over [2][pslices][R]; the rows of slices past the last one return at once
-            const long long nr = 2LL * a.pslices * a.R;
-            hipLaunchKernelGGL((bwd_reduce<TWO_D>), dim3((unsigned)nr), dim3(64), 0, st, b);
+    const bool streams = BF16 && bwd_streams(a, TWO_D);
+    if (streams && !PL && !LIN) {
+        if ((e = launch_bwd_query(a, TWO_D, st)) != hipSuccess) return e;
+    } else if constexpr (BF16 && NW == 4 && !PL && !LIN) {
+        return hipErrorInvalidValue;   // blocks of 128 queries and more always stream
+    } else {
+        // the query pass and the reduction of its partials, pslices slices at a time
+        for (int s0 = 0; s0 < a.nslice; s0 += a.pslices) {
+            BwdArgs b = a;
+            b.slice0 = s0;
+            const int cnt = a.nslice - s0 < a.pslices ? a.nslice - s0 : a.pslices;
+            hipLaunchKernelGGL((bwd_query<BF16, TWO_D, NW, PL, LIN>), dim3((unsigned)(cnt * per_slice)), dim3(64 * NW), 0,
+                               st, b);
             if ((e = hipGetLastError()) != hipSuccess) return e;
+            if (a.lv.nlev > 0) {
+                // grid over [2][pslices][R]; the rows of slices past the last one return at once
+                const long long nr = 2LL * a.pslices * a.R;
+                hipLaunchKernelGGL((bwd_reduce<TWO_D>), dim3((unsigned)nr), dim3(64), 0, st, b);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+            }
         }
     }
-    if (BF16 && bwd_streams(a, TWO_D)) {
+    if (streams) {
         if ((e = launch_bwd_key(a, TWO_D, st)) != hipSuccess) return e;
     } else if constexpr (BF16 && NW == 4) {
-        return hipErrorInvalidValue;   // blocks of 128 queries and more always stream
+        return hipErrorInvalidValue;
     } else {
         const unsigned groups = (unsigned)((long long)a.nslice * per_slice);
         hipLaunchKernelGGL((bwd_key<BF16, TWO_D, NW>), dim3(groups), dim3(64 * NW), 0, st, a);

@@ -7,6 +7,532 @@ namespace fma_dev {
 
 namespace {
 
+// ---------------------------------------------------------------- query pass
+// Gradients of the queries: the near window's keys and the interaction-list
+// rows, with the softmax's reference maximum and sum formed on the way
+// (dq = sum exp2(s - m)(dP - D) k, dQ = tau dq / l at the end), and lse, D of
+// every query for the other passes.
+//
+// Bounds, at 1D 65536 x 128, 32 slices: it reads Q, K, V, O, dO and writes dQ
+// once, 1.6 GB (310 us at a copy's 5.2 TB/s).  The coarse rows' gradients are
+// a pass of their own (bwd_coarse_mfma): kept in this kernel, they needed the
+// queries' transposes in LDS (61 KB a workgroup, two waves per SIMD) and four
+// barriers per 32 slots.  With them apart, 37 KB and three waves per SIMD.
+// Query pass with the coarse pass and the reduction of its partial rows:
+// 1D 65536 x 128 918 -> 711 us, causal 16384 x 128 (96 slices) 591 -> 486 us,
+// 128 x 128 map (128 slices) 2890 -> 1119 us, blocks of 32 (64 slices of
+// 4000) 296 -> 98 us.
+constexpr int kQTab = 768;   // list rows of a group: 1D <= 4 blocks x 192, 2D <= 576
+
+struct QuerySmem {
+    __bf16 k[2][TILEE];
+    __bf16 v[2][TILEE];
+    int crow[kQTab];                  // coarse row of every list row of the group (-1: empty)
+    uint32_t vis[2][kQTab / 32];      // 2D pairs: which rows each cell sees (else [0])
+    SetTab st;
+};
+
+template <int GEOM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void bwd_query_mfma(BwdArgs a)
+{
+    constexpr bool TWO_D = GEOM != GEOM_1D;
+    constexpr int K = TWO_D ? kSlots2D : kSlots1D;
+    __shared__ __attribute__((aligned(16))) QuerySmem sm;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int gps = (int)row_groups<GEOM>(a);
+    const int slice = (int)(id / (unsigned)gps);
+    const int grp = (int)(id - (unsigned)slice * (unsigned)gps);
+    const RowGroup m = row_group<GEOM, false>(a, grp, wave);
+    load_sets(sm.st, a, tid);
+
+    const char *const kg = static_cast<const char *>(a.k) + (long long)slice * a.n * ROWB;
+    const char *const vg = static_cast<const char *>(a.v) + (long long)slice * a.n * ROWB;
+    const char *const kb = static_cast<const char *>(a.kbar) + (long long)slice * a.R * ROWB;
+    const char *const vb = static_cast<const char *>(a.vbar) + (long long)slice * a.R * ROWB;
+    const int loff = dma_lane_off(lane, wave & 1);
+
+    // list rows of the group, in 32-row pieces: 1D every block's own list, one
+    // after the other; 2D pairs the slots of their sibling group (group_slots:
+    // level-1 window, shared lists), seen by each cell through a bit mask;
+    // 16 x 16 cells their own list.
+    const int b0 = GEOM == GEOM_1D ? 128 * grp / a.r : 0;
+    const int b1 = GEOM == GEOM_1D ? (128 * grp + 96 < a.n ? 128 * grp + 96 : (int)a.n - 32) / a.r : 0;
+    const int nslot = a.lv.nlev == 0 ? 0 : GEOM == GEOM_2DP ? a.gslot : a.nslot;
+    const int npc = (nslot + 31) / 32;                           // pieces per list
+    const int npiece = (b1 - b0 + 1) * npc;
+    const int nct = (npiece + 1) / 2;                            // coarse tiles
+    const int pc0 = GEOM == GEOM_1D ? (m.blk - b0) * npc : 0;    // this wave's pieces [pc0, pc0 + npc)
+
+    // Tile t into stage st: wave w loads rows 8 w .. and 8 (w + 4) .. of K and V
+    auto issue = [&](int t, int st) {
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+            const int i = wave + 4 * jj;
+            const uint32_t kd = lds_u32(sm.k[st]) + i * 1024, vd = lds_u32(sm.v[st]) + i * 1024;
+            if (t < m.ntile) {
+                const long long o = tile_run<GEOM>(a, m, t, i) * ROWB + loff;
+                dma16(kg + o, kd);
+                dma16(vg + o, vd);
+            } else {
+                // gathered rows; empty ones read coarse row 0 (their weight is 0)
+                const int row = sm.crow[(t - m.ntile) * KT + 8 * i + (lane >> 3)];
+                const long long o = (long long)(row < 0 ? 0 : row) * ROWB + loff - (lane >> 3) * ROWB;
+                dma16(kb + o, kd);
+                dma16(vb + o, vd);
+            }
+        }
+    };
+    issue(0, 0);
+
+    // this lane's query and its upstream gradient, D = dO . O
+    const long long qtok = m.active ? wave_token<GEOM>(a, m, m.pos0 + l32) : 0;
+    const long long qrow = ((long long)slice * a.n + qtok) * kHeadDim;
+    RowOp<true> qo, go;
+    float dpart = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        qo.x[c] = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(a.q) + qrow + 16 * c + 8 * hh);
+        go.x[c] = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(a.dout) + qrow + 16 * c + 8 * hh);
+        const bf16x8 o = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(a.out) + qrow + 16 * c + 8 * hh);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dpart += static_cast<float>(go.x[c][e]) * static_cast<float>(o[e]);
+    }
+    const float dd = psum(dpart);
+    __syncthreads();   // the set tables
+    for (int e0 = 64 * wave; e0 < nct * KT; e0 += 256) {
+        const int e = e0 + lane;
+        int row = -1, mask = 0;
+        if constexpr (GEOM == GEOM_1D) {
+            const int bl = e / (32 * npc), sl = e - bl * 32 * npc;
+            if (bl <= b1 - b0 && sl < nslot) {
+                const int set = sl / K;
+                const int g = list1d_entry(b0 + bl, sm.st.lvl[set], sl - set * K, sm.st.M[set], a.causal);
+                if (g >= 0) {
+                    row = sm.st.off[set] + g;
+                    mask = 1;
+                }
+            }
+        } else {
+            const int cx = GEOM == GEOM_2DP ? grp / ((a.nby + 1) >> 1) : m.blk / a.nby;
+            const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * ((a.nby + 1) >> 1)) : m.blk - (m.blk / a.nby) * a.nby;
+            if (e < nslot) {
+                const int nw = GEOM == GEOM_2DP ? a.rank * group_window(1) : 0;
+                if (e < nw) {
+                    const int set = e / 36, pos = e - set * 36;
+                    const int u = 2 * (cx >> 1) - 2 + pos / 6, v = 2 * (cy >> 1) - 2 + pos % 6;
+                    if (u >= 0 && u < sm.st.M[set] && v >= 0 && v < sm.st.My[set]) {
+                        row = sm.st.off[set] + u * sm.st.My[set] + v;
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const int du = u - cx, dv = v - cy - c;
+                            mask |= (du < -1 || du > 1 || dv < -1 || dv > 1) ? 1 << c : 0;
+                        }
+                    }
+                } else {
+                    const int set = (GEOM == GEOM_2DP ? a.rank : 0) + (e - nw) / K, j = (e - nw) % K;
+                    const int g = list2d_entry(cx, cy, sm.st.lvl[set], j, sm.st.M[set], sm.st.My[set]);
+                    if (g >= 0) {
+                        row = sm.st.off[set] + g;
+                        mask = 3;
+                    }
+                }
+            }
+        }
+        sm.crow[e] = row;
+#pragma unroll
+        for (int c = 0; c < (GEOM == GEOM_2DP ? 2 : 1); ++c) {
+            const unsigned long long b = __builtin_amdgcn_ballot_w64((mask >> c) & 1);
+            if (lane == 0) {
+                sm.vis[c][e0 / 32] = (uint32_t)b;
+                sm.vis[c][e0 / 32 + 1] = (uint32_t)(b >> 32);
+            }
+        }
+    }
+
+    const float cs = a.scale_log2;
+    const RowOff ro = row_offsets(l32, hh);
+    const TrOff to = tr_offsets(lane);
+    f32x16 dq0 = {0}, dq1 = {0};
+    float mrun = 0.f, lrun = 0.f;
+    bool first = true;
+    // one 32-row piece; mode 0: every row visible, 1: causal diagonal (row <=
+    // query), 2: rows whose bit 8 (i >> 2) + (i & 3) of mw is set
+    auto piece = [&](const __bf16 *kt, const __bf16 *vt, int mode, uint32_t mw) {
+        RowOp<true> rop;
+        read_row(rop, kt, ro);
+        f32x16 s = contract_channels<true>(rop, qo, f32x16{0});   // S^T: keys x queries
+        __builtin_amdgcn_sched_barrier(0);
+        read_row(rop, vt, ro);
+        f32x16 dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dp[i] = -dd;
+        dp = contract_channels<true>(rop, go, dp);                // dP^T - D
+        __builtin_amdgcn_sched_barrier(0);
+        auto mask_rows = [&](f32x16 &x) {
+            if (mode == 1) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = acc_row(i, hh) <= l32 ? x[i] : -INFINITY;
+            } else if (mode == 2) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = (mw >> (8 * (i >> 2) + (i & 3))) & 1u ? x[i] : -INFINITY;
+            }
+        };
+        mask_rows(s);
+        if (first) {
+            // a near piece: every query sees at least one of its rows
+            float mx = s[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+            mrun = pmax(mx) * cs;
+            first = false;
+        }
+        // P against the reference maximum as it stands (it only keeps P
+        // finite); when a lane's sum passes 2^64 the piece's scores are formed
+        // again, m is raised to their maximum and l, dq rescaled
+        float bl = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            s[i] = fexp2(fmaf(s[i], cs, -mrun));
+            bl += s[i];
+        }
+        if (__builtin_amdgcn_ballot_w64(bl > 0x1p64f) != 0) {
+            read_row(rop, kt, ro);
+            f32x16 s2 = contract_channels<true>(rop, qo, f32x16{0});
+            mask_rows(s2);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                s2[i] *= cs;
+                mx = fmaxf(mx, s2[i]);
+            }
+            const float mnew = fmaxf(mrun, pmax(mx));
+            const float corr = fexp2(mrun - mnew);
+            lrun *= corr;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                dq0[i] *= corr;
+                dq1[i] *= corr;
+            }
+            mrun = mnew;
+            bl = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                s[i] = fexp2(s2[i] - mrun);
+                bl += s[i];
+            }
+        }
+        lrun += bl;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] *= dp[i];   // dS
+        bf16x8 sb[2];
+        pack_b(s, sb);
+        contract_tr(kt, to, sb, dq0, dq1);
+    };
+
+    const int ntile = m.ntile + nct;
+    for (int t = 0; t < ntile; ++t) {
+        const int st = t & 1;
+        wait_vm<0>();
+        __syncthreads();
+        if (t + 1 < ntile) issue(t + 1, st ^ 1);
+#pragma unroll 1
+        for (int hb = 0; hb < 2; ++hb) {
+            const __bf16 *kt = sm.k[st] + hb * 32 * kHeadDim, *vt = sm.v[st] + hb * 32 * kHeadDim;
+            int mode = 0;
+            uint32_t mw = 0;
+            if (t < m.ntile) {
+                if (!tile_used<GEOM>(m, t, hb)) continue;
+                if (!TWO_D && t * KT + 32 * hb == m.wdiag) mode = 1;
+            } else {
+                const int pc = 2 * (t - m.ntile) + hb;
+                if (!m.active || pc < pc0 || pc >= pc0 + npc) continue;
+                mw = sm.vis[GEOM == GEOM_2DP ? wave >> 1 : 0][pc] >> (4 * hh);
+                mode = 2;
+            }
+            piece(kt, vt, mode, mw);
+        }
+    }
+    if (!m.active) return;
+    const float lsum = psum(lrun);
+    if (hh == 0) {
+        a.lse[(long long)slice * a.n + qtok] = mrun + __log2f(lsum);
+        a.delta[(long long)slice * a.n + qtok] = dd;
+    }
+    const float f = lsum > 0.f ? a.scale / lsum : 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        dq0[i] *= f;
+        dq1[i] *= f;
+    }
+    store_rows(static_cast<__bf16 *>(a.dq) + (long long)slice * a.n * kHeadDim, dq0, dq1, lane,
+               [&](int row) { return wave_token<GEOM>(a, m, m.pos0 + row); });
+}
+
+// --------------------------------------------------------- coarse-row pass
+// Partial gradients of the coarse rows, dK_bar = tau Q^T dS and dV_bar = dO^T P
+// over the queries of one sibling group (group_slots): one wave per (slice,
+// group, 32 slots), the slots' rows in registers, the group's queries in
+// 32-row chunks through a ring of two private LDS stages: no barrier, no sums
+// between waves.  A slot that a block of the group does not list (the level-1
+// window's near squares, or a group past the map) is masked for its chunks.
+// Sharing one partial row among the siblings is what makes it cheap in 2D: 90
+// rows per four cells of a three-level map instead of 4 x 81, 0.38 GB of
+// partials instead of 1.36 (2D at 128 slices: 235 us, 104 us in 1D at 96).
+struct CoarseSmem {
+    __bf16 q[2][32 * kHeadDim];
+    __bf16 g[2][32 * kHeadDim];
+    __attribute__((aligned(16))) float ld[2][64];   // lse of the chunk's rows, then D
+};
+
+template <bool TWO_D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 3))) void bwd_coarse_mfma(BwdArgs a)
+{
+    constexpr int K = TWO_D ? kSlots2D : kSlots1D;
+    __shared__ __attribute__((aligned(16))) CoarseSmem sm;
+    const int lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
+    const int npc = (a.gslot + 31) / 32;
+    const unsigned id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int pc = (int)(id % (unsigned)npc);
+    const unsigned gid = id / (unsigned)npc;
+    const int ls = (int)(gid / (unsigned)a.ngrp), grp = (int)(gid - (unsigned)ls * (unsigned)a.ngrp);
+    const int slice = a.slice0 + ls;
+
+    // the group's blocks: 1D blocks 2 grp, 2 grp + 1; 2D cells (cx0 + i, cy0 + j)
+    int cx0 = 2 * grp, cy0 = 0, ncx, ncy = 1, cpb;   // blocks per axis, chunks per block
+    if constexpr (TWO_D) {
+        const int ngy = (a.nby + 1) >> 1;
+        cx0 = 2 * (grp / ngy);
+        cy0 = 2 * (grp - (grp / ngy) * ngy);
+        ncy = a.nby - cy0 < 2 ? 1 : 2;
+        cpb = a.r * a.r / 32;
+    } else {
+        cpb = a.r / 32;
+    }
+    ncx = a.nbx - cx0 < 2 ? 1 : 2;
+    const int nchunk = ncx * ncy * cpb;
+
+    // this lane's slot: its coarse row and the blocks (bit 2 i + j) that list it
+    const int slot = pc * 32 + l32;
+    int row = 0, mask = 0;
+    if (slot < a.gslot) {
+        const int nw = a.rank * group_window(TWO_D);
+        if (slot < nw) {
+            const int set = slot / group_window(TWO_D), pos = slot - set * group_window(TWO_D);
+            const int u = cx0 - 2 + (TWO_D ? pos / 6 : pos), v = TWO_D ? cy0 - 2 + pos % 6 : 0;
+            if (u >= 0 && u < a.lv.M[set] && (!TWO_D || (v >= 0 && v < a.lv.My[set]))) {
+                row = a.lv.off[set] + (TWO_D ? u * a.lv.My[set] + v : u);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < (TWO_D ? 2 : 1); ++j) {
+                        const int du = u - cx0 - i, dv = v - cy0 - j;
+                        bool near = du >= -1 && du <= 1 && (!TWO_D || (dv >= -1 && dv <= 1));
+                        if (!TWO_D && a.causal) near = du > -2;
+                        mask |= near ? 0 : 1 << (2 * i + j);
+                    }
+            }
+        } else {
+            const int set = a.rank + (slot - nw) / K, j = (slot - nw) % K;
+            int g;
+            if constexpr (TWO_D)
+                g = list2d_entry(cx0, cy0, a.lv.lvl[set], j, a.lv.M[set], a.lv.My[set]);
+            else
+                g = list1d_entry(cx0, a.lv.lvl[set], j, a.lv.M[set], a.causal);
+            if (g >= 0) {
+                row = a.lv.off[set] + g;
+                mask = 15;
+            }
+        }
+    }
+    RowOp<true> ko, vn;   // the slot's rows (V negated, as in the key pass)
+    const long long crow = ((long long)slice * a.R + row) * kHeadDim;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        ko.x[c] = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(a.kbar) + crow + 16 * c + 8 * hh);
+        uint4 v = *reinterpret_cast<const uint4 *>(static_cast<const __bf16 *>(a.vbar) + crow + 16 * c + 8 * hh);
+        v.x ^= 0x80008000u;
+        v.y ^= 0x80008000u;
+        v.z ^= 0x80008000u;
+        v.w ^= 0x80008000u;
+        vn.x[c] = __builtin_bit_cast(bf16x8, v);
+    }
+
+    const char *const qg = static_cast<const char *>(a.q) + (long long)slice * a.n * ROWB;
+    const char *const gg = static_cast<const char *>(a.dout) + (long long)slice * a.n * ROWB;
+    const float *const lg = a.lse + (long long)slice * a.n;
+    const float *const dg = a.delta + (long long)slice * a.n;
+    const int loff0 = dma_lane_off(lane, 0), loff1 = dma_lane_off(lane, 1);
+    const int lgr = 31 - __builtin_clz(a.r);
+    auto block_of = [&](int c, int &i, int &j, int &p) {   // block (i, j) of chunk c and the chunk's position in it
+        const int b = c / cpb;
+        i = b / ncy;
+        j = b - i * ncy;
+        p = 32 * (c - b * cpb);
+    };
+    auto run_tok = [&](int c, int i8) {   // first token of rows 8 i8 .. of chunk c
+        int i, j, p;
+        block_of(c, i, j, p);
+        p += 8 * i8;
+        if constexpr (TWO_D)
+            return (long long)(((cx0 + i) << lgr) + (p >> lgr)) * a.side + ((cy0 + j) << lgr) + (p & (a.r - 1));
+        else
+            return (long long)(cx0 + i) * a.r + p;
+    };
+    auto issue = [&](int c, int st) {   // nine loads
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const long long o = run_tok(c, i) * ROWB + ((i & 1) ? loff1 : loff0);
+            dma16(qg + o, lds_u32(sm.q[st]) + i * 1024);
+            dma16(gg + o, lds_u32(sm.g[st]) + i * 1024);
+        }
+        dma4((hh ? dg : lg) + run_tok(c, l32 >> 3) + (l32 & 7), lds_u32(sm.ld[st]));
+    };
+    issue(0, 0);
+
+    const float cs = a.scale_log2;
+    const RowOff ro = row_offsets(l32, hh);
+    const TrOff to = tr_offsets(lane);
+    f32x16 dk0 = {0}, dk1 = {0}, dv0 = {0}, dv1 = {0};
+    for (int c = 0; c < nchunk; ++c) {
+        const int st = c & 1;
+        if (c + 1 < nchunk) {
+            __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));   // the other stage's reads are done
+            issue(c + 1, st ^ 1);
+            wait_vm<9>();
+        } else {
+            wait_vm<0>();
+        }
+        int bi, bj, bp;
+        block_of(c, bi, bj, bp);
+        const bool on = (mask >> (2 * bi + bj)) & 1;
+        RowOp<true> rop;
+        read_row(rop, sm.q[st], ro);
+        f32x16 s = contract_channels<true>(rop, ko, f32x16{0});   // S: queries x slots
+        __builtin_amdgcn_sched_barrier(0);
+        read_row(rop, sm.g[st], ro);
+        f32x16 dp;
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+            const f32x4 d4 = *reinterpret_cast<const f32x4 *>(&sm.ld[st][32 + 8 * c4 + 4 * hh]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dp[4 * c4 + e] = d4[e];
+        }
+        dp = contract_channels<true>(rop, vn, dp);                // D - dP
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 p;
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+            const f32x4 l4 = *reinterpret_cast<const f32x4 *>(&sm.ld[st][8 * c4 + 4 * hh]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                p[4 * c4 + e] = fexp2(fmaf(s[4 * c4 + e], cs, -l4[e]));
+                s[4 * c4 + e] = p[4 * c4 + e] * dp[4 * c4 + e];   // -dS
+            }
+        }
+        bf16x8 pb[2], sb[2];
+        pack_b(p, pb);
+        pack_b(s, sb);
+        if (__builtin_amdgcn_ballot_w64(!on) != 0) {
+            // bitwise, so that a masked slot's weights are 0 whatever they were
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const uint32_t keep = on ? 0xffffffffu : 0u;
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                u32x4 x = __builtin_bit_cast(u32x4, pb[hf]), y = __builtin_bit_cast(u32x4, sb[hf]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] &= keep;
+                    y[e] &= keep;
+                }
+                pb[hf] = __builtin_bit_cast(bf16x8, x);
+                sb[hf] = __builtin_bit_cast(bf16x8, y);
+            }
+        }
+        contract_tr(sm.g[st], to, pb, dv0, dv1);   // dO^T P
+        contract_tr(sm.q[st], to, sb, dk0, dk1);   // -Q^T dS
+    }
+    const long long base = (((long long)ls * a.ngrp + grp) * a.gslot + pc * 32) * kHeadDim;
+    const long long half = (long long)a.pslices * a.ngrp * a.gslot * kHeadDim;
+    auto rowptr = [&](float *b) {
+        return [&, b](int r) { return pc * 32 + r < a.gslot ? b + r * kHeadDim : static_cast<float *>(nullptr); };
+    };
+    store_rows_f32(dk0, dk1, -a.scale, lane, rowptr(a.part + base));
+    store_rows_f32(dv0, dv1, 1.f, lane, rowptr(a.part + half + base));
+}
+
+// dK_bar, dV_bar of every coarse row: one wave per (tensor, slice, row), the
+// partial rows of the sibling groups whose lists hold it in a fixed order,
+// dealt to eight lane groups (deal_box).  Level 1: the parents next to the
+// row's own (3 per axis), slot = place in the parent's window; level l >= 2:
+// the sibling groups inside the level-l groups that list it (list inverse).
+template <bool TWO_D>
+__global__ __launch_bounds__(64) void bwd_group_reduce(BwdArgs a)
+{
+    constexpr int K = TWO_D ? kSlots2D : kSlots1D, KW = group_window(TWO_D);
+    constexpr int NC = TWO_D ? 49 : 7;
+    __shared__ int cand_j[NC];
+    const long long wg = blockIdx.x;
+    const int tid = threadIdx.x;
+    const int z = (int)(wg / ((long long)a.pslices * a.R));
+    const long long rem = wg - (long long)z * a.pslices * a.R;
+    const int ls = (int)(rem / a.R);
+    const int crow = (int)(rem - (long long)ls * a.R);
+    const int slice = a.slice0 + ls;
+    if (z > 1 || slice >= a.nslice) return;
+    int e = 0;
+    while (e + 1 < a.lv.nlev && a.lv.off[e + 1] <= crow) ++e;
+    const int lvl = a.lv.lvl[e], M = a.lv.M[e], My = a.lv.My[e];
+    const int g = crow - a.lv.off[e];
+    const int u = TWO_D ? g / My : g, v = TWO_D ? g - (g / My) * My : 0;
+    const int ngx = (a.nbx + 1) >> 1, ngy = TWO_D ? (a.nby + 1) >> 1 : 1;   // sibling groups per axis
+    const int grp = tid >> 3, c8 = (tid & 7) * 8;
+    const long long zoff = ((long long)z * a.pslices + ls) * a.ngrp * a.gslot * kHeadDim;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto add = [&](int px, int py, int slot) {
+        const long long pr = TWO_D ? (long long)px * ngy + py : px;
+        add8(acc, a.part, zoff + (pr * a.gslot + slot) * kHeadDim + c8, a.part_elems);
+    };
+    if (lvl == 1) {
+        const int px0 = (u >> 1) > 0 ? (u >> 1) - 1 : 0, px1 = (u >> 1) + 1 < ngx ? (u >> 1) + 1 : ngx - 1;
+        const int py0 = TWO_D && (v >> 1) > 0 ? (v >> 1) - 1 : 0, py1 = TWO_D && (v >> 1) + 1 < ngy ? (v >> 1) + 1 : ngy - 1;
+        deal_box<8>(px1 - px0 + 1, py1 - py0 + 1, 1, grp, 0, [&](int dx, int dy, int) {
+            const int px = px0 + dx, py = py0 + dy;
+            const int au = u - (2 * px - 2), av = v - (2 * py - 2);
+            add(px, py, e * KW + (TWO_D ? au * 6 + av : au));
+        });
+    } else {
+        const int span = 1 << (lvl - 2);   // sibling groups per level group and axis
+        if (tid < NC) {
+            int jj = -1;
+            if constexpr (TWO_D) {
+                const int qx = u - 3 + tid / 7, qy = v - 3 + tid % 7;
+                if (qx >= 0 && qy >= 0 && qx < M && qy < My && qx * span < ngx && qy * span < ngy)
+                    jj = list2d_slot_of(qx, qy, u, v);
+            } else {
+                const int q = g - 3 + tid;
+                if (q >= 0 && q < M && q * span < ngx)
+                    for (int j = 0; j < K; ++j)
+                        if (list1d_entry(2 * q * span, lvl, j, M, a.causal) == g) jj = j;
+            }
+            cand_j[tid] = jj;
+        }
+        __syncthreads();
+        int t0 = 0;
+        for (int c = 0; c < NC; ++c) {
+            const int j = cand_j[c];
+            if (j < 0) continue;
+            const int slot = a.rank * KW + (e - a.rank) * K + j;
+            const int px0 = (TWO_D ? u - 3 + c / 7 : g - 3 + c) * span, py0 = TWO_D ? (v - 3 + c % 7) * span : 0;
+            const int nx = ngx - px0 < span ? ngx - px0 : span, ny = TWO_D ? (ngy - py0 < span ? ngy - py0 : span) : 1;
+            deal_box<8>(nx, ny, 1, grp, t0, [&](int dx, int dy, int) { add(px0 + dx, py0 + dy, slot); });
+            t0 += nx * ny;
+        }
+    }
+    store_group_sums(acc, grp, z ? a.dvbar : a.dkbar, ((long long)slice * a.R + crow) * kHeadDim + c8, a.coarse_elems, true);
+}
+
 // ------------------------------------------------------------------ key pass
 // Gradients of the keys and values: dk, dv from the queries of the near window
 // and, through the coarsening, from dK_bar, dV_bar of every coarse set; plus
@@ -280,6 +806,34 @@ hipError_t launch_key(const BwdArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+template <int GEOM>
+hipError_t launch_query(const BwdArgs &a, hipStream_t st)
+{
+    constexpr bool TWO_D = GEOM != GEOM_1D;
+    const long long groups = (long long)a.nslice * row_groups<GEOM>(a);
+    const int nslot = GEOM == GEOM_2DP ? a.gslot : a.nslot;
+    const long long lists = GEOM == GEOM_1D && a.r < 128 ? 128 / a.r : 2;   // blocks a 1D group can span
+    if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
+    if ((GEOM == GEOM_1D ? lists : 1) * ((nslot + 31) / 32) * 32 > kQTab) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((bwd_query_mfma<GEOM>), dim3((unsigned)groups), dim3(256), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.lv.nlev == 0) return e;
+    // the coarse rows' gradients, pslices slices at a time
+    if (a.pslices <= 0 || 2LL * a.pslices * a.ngrp * a.gslot * kHeadDim > a.part_elems) return hipErrorInvalidValue;
+    for (int s0 = 0; s0 < a.nslice; s0 += a.pslices) {
+        BwdArgs b = a;
+        b.slice0 = s0;
+        const int cnt = a.nslice - s0 < a.pslices ? a.nslice - s0 : a.pslices;
+        const long long units = (long long)cnt * a.ngrp * ((a.gslot + 31) / 32), rows = 2LL * a.pslices * a.R;
+        if (units > 0x7fffffffLL || rows > 0x7fffffffLL) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((bwd_coarse_mfma<TWO_D>), dim3((unsigned)units), dim3(64), 0, st, b);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_group_reduce<TWO_D>), dim3((unsigned)rows), dim3(64), 0, st, b);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace
 
 // Blocks that the 128-row groups cut into whole 32-row chunks: every 1D block
@@ -291,6 +845,13 @@ bool bwd_streams(const BwdArgs &a, bool two_d)
     // 32-bit tokens and coarse-row element offsets
     if (a.n > 0x7fffffffLL - 4096 || (long long)a.R * kHeadDim > 0x7fffffffLL) return false;
     return two_d ? a.r == 8 || a.r == 16 : a.r % 32 == 0;
+}
+
+hipError_t launch_bwd_query(const BwdArgs &a, bool two_d, hipStream_t st)
+{
+    if (!bwd_streams(a, two_d)) return hipErrorInvalidValue;
+    if (!two_d) return launch_query<GEOM_1D>(a, st);
+    return a.r == 8 ? launch_query<GEOM_2DP>(a, st) : launch_query<GEOM_2D>(a, st);
 }
 
 hipError_t launch_bwd_key(const BwdArgs &a, bool two_d, hipStream_t st)

@@ -81,6 +81,7 @@ struct fma_plan_s {
     // backward workspace: the forward's, then lse, D, coarse partials,
     // dK_bar / dV_bar and the weight-gradient dot products (256-byte aligned)
     int npart_max;         // backward: coarse-partial rows per slice, one per (query block, workgroup)
+    int bw_ngrp, bw_gslot; // backward: sibling groups per slice and their list slots (0: partials per block)
     int bw_pslices;        // backward: slices per pass of the query pass and its reduction
     size_t bw_part_floats; // backward: floats of the partials' space
     size_t bw_lse, bw_delta, bw_part, bw_cbar, bw_dot, bw_bytes;
@@ -497,7 +498,15 @@ fma_status_t fma_plan(const fma_desc_t *d, fma_plan_t *out)
         // it (at least one slice a pass), so that the workspace does not grow
         // with a partial row per slice of the whole batch; the 2D weight
         // gradients' line sums reuse the space
-        const size_t per_slice = nlev > 0 ? (size_t)2 * p.npart_max * p.nslot * fma_dev::kHeadDim : 0;
+        size_t per_slice = nlev > 0 ? (size_t)2 * p.npart_max * p.nslot * fma_dev::kHeadDim : 0;
+        // bf16 plans under the joint normalisation on streamed 128-row groups
+        // (see bwd_streams): one partial row per sibling group and slot
+        if (nlev > 0 && d->dtype == FMA_BF16 && !p.norm_level && !p.linear &&
+            (d->ndim == 1 ? p.r % 32 == 0 : p.r >= 8)) {
+            p.bw_ngrp = d->ndim == 1 ? (int)cdiv(p.nblocks, 2) : (int)(cdiv(p.nbx, 2) * cdiv(p.nby, 2));
+            p.bw_gslot = fma_dev::group_slots(d->ndim == 2, rank, nlev);
+            per_slice = (size_t)2 * p.bw_ngrp * p.bw_gslot * fma_dev::kHeadDim;
+        }
         const size_t budget = (size_t)384 << 18;   // floats
         p.bw_pslices = p.nslice > 0 ? p.nslice : 1;
         if (per_slice > 0 && (size_t)p.bw_pslices * per_slice > budget) {
@@ -1009,6 +1018,8 @@ fma_status_t backward_impl(const char *fn, fma_plan_t p, const void *q, const vo
     a.io_elems = (long long)sn * fma_dev::kHeadDim;
     a.coarse_elems = (long long)cb;
     a.part_elems = (long long)p->bw_part_floats;
+    a.ngrp = p->bw_ngrp;
+    a.gslot = p->bw_gslot;
     a.slice0 = 0;
     a.pslices = p->bw_pslices;
     a.dot_elems = (long long)sn * nlev;

@@ -102,6 +102,9 @@ struct BwdArgs {
     int npart;            // coarse-partial rows per slice: one per (query block, workgroup of the
                           // query pass); set by the backward launcher
     int nslice, heads, heads_w;
+    int ngrp, gslot;      // bf16 joint plans on streamed groups: sibling groups per slice (1D pairs of
+                          // blocks, 2D 2 x 2 cells) and list slots of a group; the partials are then
+                          // [2][pslices][ngrp][gslot][64].  0: one partial row per (block, workgroup)
     int slice0, pslices;  // the query pass and its reduction run over slices [slice0, slice0 + pslices)
                           // at a time, so that the partials need pslices slices of space
     int R, causal, nslot, rank;
@@ -113,6 +116,17 @@ struct BwdArgs {
     long long io_elems, coarse_elems, part_elems, dot_elems, lse_elems, w_elems;
     Levels lv;
 };
+
+// List slots of a sibling group of base blocks (1D: the pair 2p, 2p + 1; 2D:
+// the 2 x 2 cells of a parent square): siblings share every list from level
+// 2 on, and their level-1 lists lie in one 6-wide window (6 groups in 1D, 36
+// squares in 2D), so a group holds rank * (6 or 36) window slots, then the
+// slots of levels 2 .. L-1 as every block has them.
+__host__ __device__ constexpr int group_window(int two_d) { return two_d ? 36 : 6; }
+__host__ __device__ constexpr int group_slots(int two_d, int rank, int nlev)
+{
+    return rank * group_window(two_d) + (nlev - rank) * (two_d ? kSlots2D : kSlots1D);
+}
 
 enum Geometry { GEOM_1D = 0, GEOM_2D = 1, GEOM_DENSE = 2, GEOM_2DP = 3 /* 2D, cells in pairs (bf16 kernel) */ };
 
@@ -130,8 +144,10 @@ hipError_t launch_lists(int two_d, int nblocks, int nby, int causal, const Level
                         int32_t *out, hipStream_t st);
 hipError_t launch_backward(const BwdArgs &a, bool bf16, bool two_d, hipStream_t st);
 // bf16 backward on streamed 128-row groups (backward_mfma.hip): whether a
-// plan's blocks take it, and its key pass
+// plan's blocks take it; the query pass with the coarse rows' gradients (joint
+// normalisation, a.ngrp > 0) and the key pass
 bool bwd_streams(const BwdArgs &a, bool two_d);
+hipError_t launch_bwd_query(const BwdArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_bwd_key(const BwdArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_stream_ref(const void *src, long long nwords, void *dst, long long ndst, int write_every,
                              hipStream_t st);
