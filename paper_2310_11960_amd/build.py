@@ -20,7 +20,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_NAME = "libfma_mi355x.so"
 LIB_PATH = os.path.join(HERE, LIB_NAME)
-SOURCES = ["fma_api.hip", "coarsen.hip", "attend.hip", "attend_mfma.hip", "lists.hip", "backward.hip", "backward_mfma.hip",
+SOURCES = ["fma_api.hip", "coarsen.hip", "attend.hip", "attend_mfma.hip", "attend_group.hip", "lists.hip", "backward.hip", "backward_mfma.hip",
            "stream_ref.hip"]
 ARCH = "gfx950"
 

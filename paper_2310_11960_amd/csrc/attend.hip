@@ -29,6 +29,7 @@
 // the current tile is multiplied out of LDS.
 #include "fma_device.hpp"
 #include "fma_kernels.hpp"
+#include "level_weights.hpp"
 
 namespace fma_dev {
 
@@ -120,51 +121,6 @@ __device__ inline long long row_source(const AttnArgs &a, const LvTab &lt, const
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// Printed per-level normalisation of one 32-key block of coarse scores x
-// (log2 units, masked slots -inf): the keys form aligned groups of grp (4, 8,
-// 16 or 32) slots, one level each; element i of a lane holds key row
-// 8 * (i >> 2) + 4 * hh + (i & 3), so a group is 1 chunk of 4 in-lane (grp 4),
-// that chunk in both lanes of the pair lane, lane ^ 32 (8), two chunks (16) or
-// all four (32).  Each key's weight becomes lnear * exp2(x - m_g) / l_g, with
-// m_g and l_g the group's own maximum and sum; an empty group gives 0.
-__device__ inline void level_weights(f32x16 &x, float lnear, int grp)
-{
-    float cm[4], cl[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cm[c] = fmaxf(fmaxf(x[4 * c], x[4 * c + 1]), fmaxf(x[4 * c + 2], x[4 * c + 3]));
-    if (grp >= 16) {
-        cm[0] = cm[1] = fmaxf(cm[0], cm[1]);
-        cm[2] = cm[3] = fmaxf(cm[2], cm[3]);
-    }
-    if (grp >= 32) cm[0] = cm[1] = cm[2] = cm[3] = fmaxf(cm[0], cm[2]);
-    if (grp >= 8) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) cm[c] = fmaxf(cm[c], __shfl_xor(cm[c], 32));
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        cm[c] = cm[c] > -INFINITY ? cm[c] : 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * c + e] = fast_exp2(x[4 * c + e] - cm[c]);
-        cl[c] = (x[4 * c] + x[4 * c + 1]) + (x[4 * c + 2] + x[4 * c + 3]);
-    }
-    if (grp >= 16) {
-        cl[0] = cl[1] = cl[0] + cl[1];
-        cl[2] = cl[3] = cl[2] + cl[3];
-    }
-    if (grp >= 32) cl[0] = cl[1] = cl[2] = cl[3] = cl[0] + cl[2];
-    if (grp >= 8) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) cl[c] += __shfl_xor(cl[c], 32);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const float f = cl[c] > 0.0f ? lnear / cl[c] : 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * c + e] *= f;
-    }
-}
 
 // LIN (FMA-linear, query downsampling): a coarse slot of level l is scored
 // with the coarse query of the block's own level-l group (the same for every
@@ -667,6 +623,8 @@ hipError_t launch_nw(const AttnArgs &a, hipStream_t st)
 hipError_t launch_attend(const AttnArgs &a, bool bf16, int geometry, hipStream_t st)
 {
     if (a.nslice == 0 || a.tiles_per_slice == 0) return hipSuccess;
+    if (bf16 && geometry != GEOM_DENSE && group_attends(a, geometry == GEOM_2D))
+        return launch_attend_group(a, geometry == GEOM_2D, st);
     if (a.qbar) {   // FMA-linear
         if (geometry == GEOM_DENSE) return hipErrorInvalidValue;
         if (bf16) return geometry == GEOM_1D ? launch_nw<true, GEOM_1D, true>(a, st) : launch_nw<true, GEOM_2D, true>(a, st);

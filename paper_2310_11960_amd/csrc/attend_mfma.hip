@@ -1,5 +1,8 @@
 // attend_mfma.hip -- fused multilevel FMA attention for bf16 on gfx950
-// (Eq. fma1d / Eq. fma2d under one softmax per query).
+// (Eq. fma1d / Eq. fma2d under one softmax per query): a persistent stream for
+// 1D blocks that fill whole workgroups, FMA-linear, per-level maps of rank 2 and
+// more, and the dense reference; the other plans run on attend_group.hip
+// (group_attends).
 //
 // One workgroup owns one query tile: a base block of r queries (1D) or an
 // r x r cell (2D), 32 queries per wave.  It walks a list of 64-key tiles:
@@ -139,6 +142,46 @@ __device__ inline uint32_t pack_bf16(float lo, float hi)
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     const bf16x2 p = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
     return __builtin_bit_cast(uint32_t, p);
+}
+
+// A wave's O^T (rows channels, columns queries; scaled by inv) to bf16 rows of
+// 64 channels at base + token(row) * 64, in kStores store instructions.
+// Exchanges between lane halves and 16-lane rows first gather 64 consecutive
+// bytes of a row in four lanes, so that an instruction writes 16 half lines
+// instead of 8-byte pieces of 32 lines.
+constexpr int kStores = 4;
+template <typename F>
+__device__ __attribute__((always_inline)) inline void store_out(__bf16 *base, const f32x16 &o0, const f32x16 &o1,
+                                                                float inv, int lane, F token)
+{
+    const int l16 = lane & 15, chunk = 2 * ((lane >> 4) & 1) + (lane >> 5);
+    __bf16 *const r0 = base + token(l16) * kHeadDim + 8 * chunk;
+    __bf16 *const r1 = base + token(16 + l16) * kHeadDim + 8 * chunk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const f32x16 &o = h ? o1 : o0;
+        uint32_t u[8];   // channels 32 h + 8 g + 4 (lane >> 5) + 2 k, + 1 of the lane's row in u[2 g + k]
+#pragma unroll
+        for (int x = 0; x < 8; ++x) u[x] = pack_bf16(o[2 * x] * inv, o[2 * x + 1] * inv);
+        // lane halves: whole 16-byte chunks, chunk 2 x + (lane >> 5) in u[4 x .. 4 x + 3]
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const auto r = __builtin_amdgcn_permlane32_swap(u[4 * x + k], u[4 * x + 2 + k], false, false);
+                u[4 * x + k] = r[0];
+                u[4 * x + 2 + k] = r[1];
+            }
+        // 16-lane rows: u[0 .. 3] for row l16, u[4 .. 7] for row 16 + l16
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const auto r = __builtin_amdgcn_permlane16_swap(u[k], u[4 + k], false, false);
+            u[k] = r[0];
+            u[4 + k] = r[1];
+        }
+        *reinterpret_cast<uint4 *>(r0 + 32 * h) = make_uint4(u[0], u[1], u[2], u[3]);
+        *reinterpret_cast<uint4 *>(r1 + 32 * h) = make_uint4(u[4], u[5], u[6], u[7]);
+    }
 }
 
 enum TileMask { MASK_NONE = 0, MASK_CAUSAL = 1, MASK_SLOTS = 2 };
@@ -859,11 +902,11 @@ _Pragma("unroll")                                                               
     do {                                                                                                        \
         const int ahead = issued - step - 1 < NS - 2 ? issued - step - 1 : NS - 2;                              \
         if (ahead >= 2)                                                                                         \
-            stored ? wait_vmcnt<2 * NLD + 8>() : wait_vmcnt<2 * NLD>();                                         \
+            stored ? wait_vmcnt<2 * NLD + kStores>() : wait_vmcnt<2 * NLD>();                                         \
         else if (ahead == 1)                                                                                    \
-            stored ? wait_vmcnt<NLD + 8>() : wait_vmcnt<NLD>();                                                 \
+            stored ? wait_vmcnt<NLD + kStores>() : wait_vmcnt<NLD>();                                                 \
         else                                                                                                    \
-            wait_vmcnt<0>();                                                                                    \
+            stored ? wait_vmcnt<kStores>() : wait_vmcnt<0>(); \
         stored = false;                                                                                         \
         __syncthreads();                                                                                        \
         if (ivalid) FMA_ISSUE_NEXT((step + NS - 1) % NS);                                                       \
@@ -1066,18 +1109,8 @@ _Pragma("unroll")                                                               
 
         // ---------------------------------------- block done: O = O^T / l
         const float inv = 1.0f / sum_pair(lrun);
-        const long long qtok = block_token<GEOM>(cb, g, wave * 32 + l32);
-        __bf16 *op = outp + ((long long)cb.slice * g.n + qtok) * kHeadDim;
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            const int d = gq * 8 + 4 * hh;
-            *reinterpret_cast<uint2 *>(op + d) =
-                make_uint2(pack_bf16(o0[4 * gq] * inv, o0[4 * gq + 1] * inv),
-                           pack_bf16(o0[4 * gq + 2] * inv, o0[4 * gq + 3] * inv));
-            *reinterpret_cast<uint2 *>(op + 32 + d) =
-                make_uint2(pack_bf16(o1[4 * gq] * inv, o1[4 * gq + 1] * inv),
-                           pack_bf16(o1[4 * gq + 2] * inv, o1[4 * gq + 3] * inv));
-        }
+        store_out(outp + (long long)cb.slice * g.n * kHeadDim, o0, o1, inv, lane,
+                  [&](int row) { return block_token<GEOM>(cb, g, wave * 32 + row); });
         stored = true;
     }
 }
@@ -1221,7 +1254,11 @@ template <int GEOM, bool PL, bool LIN = false>
 hipError_t launch_geom(const AttnArgs &a, hipStream_t st)
 {
     switch (a.qtile / 32) {
-    case 2: return launch_nw<2, GEOM, PL, LIN>(a, st);
+    case 2:
+        if constexpr (GEOM == GEOM_1D && !LIN)
+            return hipErrorInvalidValue;   // 1D blocks of 64: always groups
+        else
+            return launch_nw<2, GEOM, PL, LIN>(a, st);
     case 4: return launch_nw<4, GEOM, PL, LIN>(a, st);
     case 6: return launch_nw<6, GEOM, PL, LIN>(a, st);
     case 8: return launch_nw<8, GEOM, PL, LIN>(a, st);
@@ -1247,6 +1284,7 @@ hipError_t launch_attend_bf16(const AttnArgs &a, int geometry, hipStream_t st)
 {
     if (a.nslice == 0 || a.tiles_per_slice == 0) return hipSuccess;
     if (a.nslot > MAX_SLOTS) return hipErrorInvalidValue;
+    if (geometry != GEOM_DENSE && group_attends(a, geometry == GEOM_2D)) return launch_attend_group(a, geometry == GEOM_2D, st);
     if (a.qbar && a.nslot > 0) {   // FMA-linear (joint normalisation, rank 1)
         if (a.norm_level || a.rank != 1) return hipErrorInvalidValue;
         if (geometry == GEOM_1D) return launch_geom<GEOM_1D, false, true>(a, st);
@@ -1262,10 +1300,7 @@ hipError_t launch_attend_bf16(const AttnArgs &a, int geometry, hipStream_t st)
         return hipErrorInvalidValue;
     }
     if (geometry == GEOM_1D) return launch_geom<GEOM_1D, false>(a, st);
-    if (geometry == GEOM_2D) {
-        if (pair_cells_2d(a.r, a.nby, a.nslot, a.norm_level, 0, 1)) return launch_nw<4, GEOM_2DP, false, false>(a, st);
-        return launch_geom<GEOM_2D, false>(a, st);
-    }
+    if (geometry == GEOM_2D) return hipErrorInvalidValue;   // joint normalisation on maps: always groups
     return launch_geom<GEOM_DENSE, false>(a, st);
 }
 

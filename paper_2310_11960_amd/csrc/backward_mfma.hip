@@ -22,13 +22,10 @@ namespace {
 // 1D 65536 x 128 918 -> 711 us, causal 16384 x 128 (96 slices) 591 -> 486 us,
 // 128 x 128 map (128 slices) 2890 -> 1119 us, blocks of 32 (64 slices of
 // 4000) 296 -> 98 us.
-constexpr int kQTab = 768;   // list rows of a group: 1D <= 4 blocks x 192, 2D <= 576
-
 struct QuerySmem {
     __bf16 k[2][TILEE];
     __bf16 v[2][TILEE];
-    int crow[kQTab];                  // coarse row of every list row of the group (-1: empty)
-    uint32_t vis[2][kQTab / 32];      // 2D pairs: which rows each cell sees (else [0])
+    ListSmem list;
     SetTab st;
 };
 
@@ -36,13 +33,12 @@ template <int GEOM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void bwd_query_mfma(BwdArgs a)
 {
     constexpr bool TWO_D = GEOM != GEOM_1D;
-    constexpr int K = TWO_D ? kSlots2D : kSlots1D;
     __shared__ __attribute__((aligned(16))) QuerySmem sm;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned id = xcd_contiguous(blockIdx.x, gridDim.x);
     const int gps = (int)row_groups<GEOM>(a);
-    const int slice = (int)(id / (unsigned)gps);
+    const int slice = __builtin_amdgcn_readfirstlane((int)(id / (unsigned)gps));
     const int grp = (int)(id - (unsigned)slice * (unsigned)gps);
     const RowGroup m = row_group<GEOM, false>(a, grp, wave);
     load_sets(sm.st, a, tid);
@@ -53,17 +49,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const char *const vb = static_cast<const char *>(a.vbar) + (long long)slice * a.R * ROWB;
     const int loff = dma_lane_off(lane, wave & 1);
 
-    // list rows of the group, in 32-row pieces: 1D every block's own list, one
-    // after the other; 2D pairs the slots of their sibling group (group_slots:
-    // level-1 window, shared lists), seen by each cell through a bit mask;
-    // 16 x 16 cells their own list.
-    const int b0 = GEOM == GEOM_1D ? 128 * grp / a.r : 0;
-    const int b1 = GEOM == GEOM_1D ? (128 * grp + 96 < a.n ? 128 * grp + 96 : (int)a.n - 32) / a.r : 0;
-    const int nslot = a.lv.nlev == 0 ? 0 : GEOM == GEOM_2DP ? a.gslot : a.nslot;
-    const int npc = (nslot + 31) / 32;                           // pieces per list
-    const int npiece = (b1 - b0 + 1) * npc;
-    const int nct = (npiece + 1) / 2;                            // coarse tiles
-    const int pc0 = GEOM == GEOM_1D ? (m.blk - b0) * npc : 0;    // this wave's pieces [pc0, pc0 + npc)
+    const GroupLists gl = group_lists<GEOM>(a, m, grp);
+    const int nnear = (m.npiece + 1) / 2, nct = (gl.npiece + 1) / 2;   // near and coarse tiles
 
     // Tile t into stage st: wave w loads rows 8 w .. and 8 (w + 4) .. of K and V
     auto issue = [&](int t, int st) {
@@ -71,13 +58,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int jj = 0; jj < 2; ++jj) {
             const int i = wave + 4 * jj;
             const uint32_t kd = lds_u32(sm.k[st]) + i * 1024, vd = lds_u32(sm.v[st]) + i * 1024;
-            if (t < m.ntile) {
-                const long long o = tile_run<GEOM>(a, m, t, i) * ROWB + loff;
+            if (t < nnear) {
+                const long long o = window_run<GEOM>(a, m, 8 * t + i) * ROWB + loff;
                 dma16(kg + o, kd);
                 dma16(vg + o, vd);
             } else {
                 // gathered rows; empty ones read coarse row 0 (their weight is 0)
-                const int row = sm.crow[(t - m.ntile) * KT + 8 * i + (lane >> 3)];
+                const int row = sm.list.crow[(t - nnear) * KT + 8 * i + (lane >> 3)];
                 const long long o = (long long)(row < 0 ? 0 : row) * ROWB + loff - (lane >> 3) * ROWB;
                 dma16(kb + o, kd);
                 dma16(vb + o, vd);
@@ -101,55 +88,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     const float dd = psum(dpart);
     __syncthreads();   // the set tables
-    for (int e0 = 64 * wave; e0 < nct * KT; e0 += 256) {
-        const int e = e0 + lane;
-        int row = -1, mask = 0;
-        if constexpr (GEOM == GEOM_1D) {
-            const int bl = e / (32 * npc), sl = e - bl * 32 * npc;
-            if (bl <= b1 - b0 && sl < nslot) {
-                const int set = sl / K;
-                const int g = list1d_entry(b0 + bl, sm.st.lvl[set], sl - set * K, sm.st.M[set], a.causal);
-                if (g >= 0) {
-                    row = sm.st.off[set] + g;
-                    mask = 1;
-                }
-            }
-        } else {
-            const int cx = GEOM == GEOM_2DP ? grp / ((a.nby + 1) >> 1) : m.blk / a.nby;
-            const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * ((a.nby + 1) >> 1)) : m.blk - (m.blk / a.nby) * a.nby;
-            if (e < nslot) {
-                const int nw = GEOM == GEOM_2DP ? a.rank * group_window(1) : 0;
-                if (e < nw) {
-                    const int set = e / 36, pos = e - set * 36;
-                    const int u = 2 * (cx >> 1) - 2 + pos / 6, v = 2 * (cy >> 1) - 2 + pos % 6;
-                    if (u >= 0 && u < sm.st.M[set] && v >= 0 && v < sm.st.My[set]) {
-                        row = sm.st.off[set] + u * sm.st.My[set] + v;
-#pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            const int du = u - cx, dv = v - cy - c;
-                            mask |= (du < -1 || du > 1 || dv < -1 || dv > 1) ? 1 << c : 0;
-                        }
-                    }
-                } else {
-                    const int set = (GEOM == GEOM_2DP ? a.rank : 0) + (e - nw) / K, j = (e - nw) % K;
-                    const int g = list2d_entry(cx, cy, sm.st.lvl[set], j, sm.st.M[set], sm.st.My[set]);
-                    if (g >= 0) {
-                        row = sm.st.off[set] + g;
-                        mask = 3;
-                    }
-                }
-            }
-        }
-        sm.crow[e] = row;
-#pragma unroll
-        for (int c = 0; c < (GEOM == GEOM_2DP ? 2 : 1); ++c) {
-            const unsigned long long b = __builtin_amdgcn_ballot_w64((mask >> c) & 1);
-            if (lane == 0) {
-                sm.vis[c][e0 / 32] = (uint32_t)b;
-                sm.vis[c][e0 / 32 + 1] = (uint32_t)(b >> 32);
-            }
-        }
-    }
+    build_lists<GEOM>(a, m, gl, grp, sm.st, nct * KT, wave, lane, sm.list);
 
     const float cs = a.scale_log2;
     const RowOff ro = row_offsets(l32, hh);
@@ -198,16 +137,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             bl += s[i];
         }
         if (__builtin_amdgcn_ballot_w64(bl > 0x1p64f) != 0) {
+            const bool raise = pmax(bl) > 0x1p64f;   // each query for itself
             read_row(rop, kt, ro);
-            f32x16 s2 = contract_channels<true>(rop, qo, f32x16{0});
-            mask_rows(s2);
+            s = contract_channels<true>(rop, qo, f32x16{0});
+            mask_rows(s);
             float mx = -INFINITY;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                s2[i] *= cs;
-                mx = fmaxf(mx, s2[i]);
-            }
-            const float mnew = fmaxf(mrun, pmax(mx));
+            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[i] * cs);
+            mx = pmax(mx);
+            const float mnew = raise ? fmaxf(mrun, mx) : mrun;
             const float corr = fexp2(mrun - mnew);
             lrun *= corr;
 #pragma unroll
@@ -219,7 +157,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             bl = 0.f;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                s[i] = fexp2(s2[i] - mrun);
+                s[i] = fexp2(fmaf(s[i], cs, -mrun));
                 bl += s[i];
             }
         }
@@ -231,7 +169,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         contract_tr(kt, to, sb, dq0, dq1);
     };
 
-    const int ntile = m.ntile + nct;
+    const int ntile = nnear + nct;
     for (int t = 0; t < ntile; ++t) {
         const int st = t & 1;
         wait_vm<0>();
@@ -242,13 +180,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             const __bf16 *kt = sm.k[st] + hb * 32 * kHeadDim, *vt = sm.v[st] + hb * 32 * kHeadDim;
             int mode = 0;
             uint32_t mw = 0;
-            if (t < m.ntile) {
-                if (!tile_used<GEOM>(m, t, hb)) continue;
+            if (t < nnear) {
+                if (!piece_used<GEOM>(a, m, 2 * t + hb)) continue;
                 if (!TWO_D && t * KT + 32 * hb == m.wdiag) mode = 1;
             } else {
-                const int pc = 2 * (t - m.ntile) + hb;
-                if (!m.active || pc < pc0 || pc >= pc0 + npc) continue;
-                mw = sm.vis[GEOM == GEOM_2DP ? wave >> 1 : 0][pc] >> (4 * hh);
+                const int pc = 2 * (t - nnear) + hb;
+                if (!m.active || pc < gl.pc0 || pc >= gl.pc0 + gl.npc) continue;
+                mw = sm.list.vis[GEOM == GEOM_2DP ? wave >> 1 : 0][pc] >> (4 * hh);
                 mode = 2;
             }
             piece(kt, vt, mode, mw);
@@ -593,7 +531,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned id = xcd_contiguous(blockIdx.x, gridDim.x);
     const int gps = (int)row_groups<GEOM>(a);
-    const int slice = (int)(id / (unsigned)gps);
+    const int slice = __builtin_amdgcn_readfirstlane((int)(id / (unsigned)gps));
     const int grp = (int)(id - (unsigned)slice * (unsigned)gps);
     const RowGroup m = row_group<GEOM, true>(a, grp, wave);
     constexpr int lgr = GEOM == GEOM_2DP ? 3 : 4;
@@ -636,12 +574,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) {
             const int i = wave + 4 * jj;
-            const long long o = tile_run<GEOM>(a, m, t, i) * ROWB + loff;
+            const long long o = window_run<GEOM>(a, m, 8 * t + i) * ROWB + loff;
             dma16(qg + o, lds_u32(sm.q[st]) + i * 1024);
             dma16(gg + o, lds_u32(sm.g[st]) + i * 1024);
         }
         if (wave < 2) {
-            const long long tok = tile_run<GEOM>(a, m, t, lane >> 3) + (lane & 7);
+            const long long tok = window_run<GEOM>(a, m, 8 * t + (lane >> 3)) + (lane & 7);
             dma4((wave == 0 ? lg : dg) + tok, lds_u32(wave == 0 ? sm.lse[st] : sm.dd[st]));
         }
     };
@@ -667,14 +605,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const TrOff to = tr_offsets(lane);
 
     f32x16 dk0 = {0}, dk1 = {0}, dv0 = {0}, dv1 = {0};
-    for (int t = 0; t < m.ntile; ++t) {
+    const int ntile = (m.npiece + 1) / 2;
+    for (int t = 0; t < ntile; ++t) {
         const int st = t & 1;
         wait_vm<0>();
         __syncthreads();
-        if (t + 1 < m.ntile) issue(t + 1, st ^ 1);
+        if (t + 1 < ntile) issue(t + 1, st ^ 1);
 #pragma unroll 1
         for (int qb = 0; qb < 2; ++qb) {
-            if (!tile_used<GEOM>(m, t, qb)) continue;
+            if (!piece_used<GEOM>(a, m, 2 * t + qb)) continue;
             const __bf16 *qt = sm.q[st] + qb * 32 * kHeadDim, *gt = sm.g[st] + qb * 32 * kHeadDim;
             // (the fences keep the two row operands from being live at once:
             // the next one's reads run under the previous one's products)
@@ -811,10 +750,8 @@ hipError_t launch_query(const BwdArgs &a, hipStream_t st)
 {
     constexpr bool TWO_D = GEOM != GEOM_1D;
     const long long groups = (long long)a.nslice * row_groups<GEOM>(a);
-    const int nslot = GEOM == GEOM_2DP ? a.gslot : a.nslot;
-    const long long lists = GEOM == GEOM_1D && a.r < 128 ? 128 / a.r : 2;   // blocks a 1D group can span
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
-    if ((GEOM == GEOM_1D ? lists : 1) * ((nslot + 31) / 32) * 32 > kQTab) return hipErrorInvalidValue;
+    if (!group_lists_fit<GEOM>(a)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_query_mfma<GEOM>), dim3((unsigned)groups), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.lv.nlev == 0) return e;

@@ -1,22 +1,10 @@
-// bwd_tiles.hpp -- what the bf16 matrix-core backward kernels share: 16-byte
-// direct-to-LDS loads, the 128-row groups a workgroup owns and the windows of
-// 64-row tiles they walk.
-//
-// A workgroup of four waves owns a group of 128 rows (queries of the query
-// pass, keys of the key pass), 32 consecutive rows of one base block per wave:
-//   1D        128 consecutive tokens, whatever the block size (a multiple of
-//             32): blocks of 32 and 64 share a workgroup, larger ones split;
-//   2D, r = 8 two horizontally adjacent cells (cx, 2c), (cx, 2c + 1), whose
-//             3x3 near windows share six cells; the last pair of an odd row
-//             has no right cell and its waves only help to load;
-//   2D, r = 16 half a cell (eight rows of it).
-// The tiles of the group's near window are loaded once for all waves; a wave
-// takes the 32-row half tiles that lie in its own window.  Every 8-row piece
-// of a tile is eight consecutive tokens, so a load's address is a uniform base
-// plus the lane's offset.
+// bwd_tiles.hpp -- what the bf16 matrix-core backward kernels share: swizzled
+// 64-row tiles filled by direct-to-LDS loads, contractions over them, result
+// stores and the sums of partial rows.
 #pragma once
 
 #include "bwd_device.hpp"
+#include "row_groups.hpp"
 
 namespace fma_dev {
 
@@ -24,175 +12,6 @@ namespace {
 
 constexpr int ROWB = 128;          // bytes of a bf16 row of 64 channels
 constexpr int TILEE = KT * 64;     // elements of one tile
-
-// 16 bytes (4 bytes) per lane from global memory to LDS byte lds_base + 16 L
-// (4 L).  Inline assembly: the compiler does not order later LDS reads
-// behind these loads, the loops wait for them explicitly (wait_vm).
-__device__ inline void dma16(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("global_load_lds_dwordx4 %0, off" : : "v"(gptr), "{m0}"(lds_base) : "memory");
-}
-__device__ inline void dma4(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("global_load_lds_dword %0, off" : : "v"(gptr), "{m0}"(lds_base) : "memory");
-}
-
-// wait until at most N vector-memory operations of this wave are in flight
-template <int N>
-__device__ inline void wait_vm()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-__device__ inline uint32_t lds_u32(const void *p)
-{
-    return __builtin_amdgcn_readfirstlane(
-        static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void *)p)));
-}
-
-// Position of workgroup `bid` of `total` when the eight XCDs, which take
-// workgroups round-robin, each walk one contiguous range: neighbouring groups,
-// which share most of their near window, meet in one XCD's L2.
-__device__ inline unsigned xcd_contiguous(unsigned bid, unsigned total)
-{
-    const unsigned x = bid & 7, j = bid >> 3, per = total >> 3, rem = total & 7;
-    return x * per + (x < rem ? x : rem) + j;
-}
-
-// A group of 128 rows: its window of tiles and this wave's part of both.
-struct RowGroup {
-    int ntile;            // 64-row tiles of the near window
-    int wlo, whi;         // this wave's window: rows [wlo, whi) of it (2D: see tile_used)
-    int wdiag;            // causal 1D: the window row where the wave's own rows start
-    bool active;          // the wave has rows
-    int blk;              // the wave's base block (1D) or cell (cx * nby + cy)
-    int pos0;             // position of the wave's first row in that block (1D: token, 2D: pixel)
-    long long lo;         // 1D: first token of the window
-    int x0, y0, ncx, cy;  // 2D: first cell row / column of the window, its cell rows; the wave's cell column
-};
-
-// Groups per slice.
-template <int GEOM>
-__host__ __device__ inline long long row_groups(const BwdArgs &a)
-{
-    if (GEOM == GEOM_1D) return (a.n + 127) / 128;
-    if (GEOM == GEOM_2DP) return (long long)a.nbx * ((a.nby + 1) / 2);
-    return 2LL * a.nbx * a.nby;
-}
-
-// Group g seen by wave `wave`.  KEYS: rows are keys and the window holds the
-// queries that may see them (causal: those at or after the key); else rows
-// are queries and the window holds their near keys.
-template <int GEOM, bool KEYS>
-__device__ inline RowGroup row_group(const BwdArgs &a, int g, int wave)
-{
-    RowGroup m;
-    m.lo = 0;
-    m.x0 = m.y0 = m.cy = 0;
-    m.ncx = 1;
-    m.wlo = 0;
-    m.whi = 0;
-    m.wdiag = -1;
-    if constexpr (GEOM == GEOM_1D) {
-        const int n = (int)a.n, r = a.r;   // tokens fit 31 bits (the launcher checks)
-        const int f0 = 128 * g, w0 = f0 + 32 * wave;
-        const int l0 = f0 + 96 < n ? f0 + 96 : n - 32;   // first row of the last active wave
-        auto lo_of = [&](int row) {
-            if (KEYS && a.causal) return row;
-            const int b = row / r;
-            return b > 0 ? (b - 1) * r : 0;
-        };
-        auto hi_of = [&](int row) {
-            if (!KEYS && a.causal) return row + 32;
-            const int h = (row / r + 2) * r;
-            return h < n ? h : n;
-        };
-        m.active = w0 < n;
-        m.blk = m.active ? w0 / r : 0;
-        m.pos0 = w0 - m.blk * r;
-        const int lo = lo_of(f0), hi = hi_of(l0);
-        m.lo = lo;
-        m.ntile = (hi - lo + KT - 1) / KT;
-        if (m.active) {
-            m.wlo = lo_of(w0) - lo;
-            m.whi = hi_of(w0) - lo;
-            if (a.causal) m.wdiag = w0 - lo;
-        }
-    } else if constexpr (GEOM == GEOM_2DP) {
-        const int npc = (a.nby + 1) >> 1;
-        const int cx = g / npc, c0 = 2 * (g - cx * npc), side = wave >> 1;
-        m.active = c0 + side < a.nby;
-        m.cy = c0 + side;
-        m.blk = m.active ? cx * a.nby + m.cy : 0;
-        m.pos0 = 32 * (wave & 1);
-        m.x0 = cx > 0 ? cx - 1 : 0;
-        m.ncx = (cx + 1 < a.nbx ? cx + 1 : cx) - m.x0 + 1;
-        m.y0 = c0 > 0 ? c0 - 1 : 0;
-        const int y1 = c0 + 2 < a.nby ? c0 + 2 : a.nby - 1;
-        m.ntile = m.ncx * (y1 - m.y0 + 1);
-    } else {
-        const int cell = g >> 1;
-        const int cx = cell / a.nby, cy = cell - cx * a.nby;
-        m.active = true;
-        m.cy = cy;
-        m.blk = cell;
-        m.pos0 = 128 * (g & 1) + 32 * wave;
-        m.x0 = cx > 0 ? cx - 1 : 0;
-        m.ncx = (cx + 1 < a.nbx ? cx + 1 : cx) - m.x0 + 1;
-        m.y0 = cy > 0 ? cy - 1 : 0;
-        const int y1 = cy + 1 < a.nby ? cy + 1 : cy;
-        m.ntile = 4 * m.ncx * (y1 - m.y0 + 1);
-    }
-    return m;
-}
-
-// First token of rows 8 i .. 8 i + 7 of window tile t (2D: column by column
-// of the window's cells).  Rows past a 1D sequence's end repeat its last ones.
-template <int GEOM>
-__device__ inline long long tile_run(const BwdArgs &a, const RowGroup &m, int t, int i)
-{
-    if constexpr (GEOM == GEOM_1D) {
-        const long long tok = m.lo + (long long)t * KT + 8 * i;
-        return tok + 8 <= a.n ? tok : a.n - 8;
-    } else if constexpr (GEOM == GEOM_2DP) {
-        const int col = t / m.ncx, row = t - col * m.ncx;
-        return (long long)((m.x0 + row) * 8 + i) * a.side + (m.y0 + col) * 8;
-    } else {
-        const int c = t >> 2, p0 = (t & 3) * KT + 8 * i;
-        const int col = c / m.ncx, row = c - col * m.ncx;
-        return (long long)((m.x0 + row) * 16 + (p0 >> 4)) * a.side + (m.y0 + col) * 16 + (p0 & 15);
-    }
-}
-
-// Whether this wave takes half hb (32 rows) of window tile t.
-template <int GEOM>
-__device__ inline bool tile_used(const RowGroup &m, int t, int hb)
-{
-    if (!m.active) return false;
-    if constexpr (GEOM == GEOM_1D) {
-        const int s0 = t * KT + 32 * hb;
-        return s0 >= m.wlo && s0 < m.whi;
-    } else if constexpr (GEOM == GEOM_2DP) {
-        const int d = m.y0 + t / m.ncx - m.cy;
-        return d >= -1 && d <= 1;
-    } else {
-        return true;
-    }
-}
-
-// Token of position p of the wave's base block
-template <int GEOM>
-__device__ inline long long wave_token(const BwdArgs &a, const RowGroup &m, int p)
-{
-    if constexpr (GEOM == GEOM_1D) {
-        return (long long)m.blk * a.r + p;
-    } else {
-        constexpr int lg = GEOM == GEOM_2DP ? 3 : 4;
-        const int cx = m.blk / a.nby, cy = m.blk - cx * a.nby;
-        return (long long)((cx << lg) + (p >> lg)) * a.side + (cy << lg) + (p & ((1 << lg) - 1));
-    }
-}
 
 // Byte offset of this lane's 16 bytes inside rows 8 i .. 8 i + 7 (odd = i & 1)
 // so that a linear direct-to-LDS load leaves chunk c of row r at position
@@ -436,23 +255,6 @@ __device__ inline int list2d_slot_of(int qx, int qy, int u, int v)
         return 6 * ox + (au - ox) * 3 + (av < oy ? av : av - 3);
     }
     return 6 * ox + 9 + (au - ox - 3) * 6 + av;
-}
-
-// Coarse-set tables in LDS (indexing the argument block with a computed
-// index per lane costs scattered loads or a copy to scratch)
-struct SetTab {
-    int lvl[kMaxSets], M[kMaxSets], My[kMaxSets], off[kMaxSets], size[kMaxSets], woff[kMaxSets];
-};
-__device__ inline void load_sets(SetTab &t, const BwdArgs &a, int tid)
-{
-    if (tid < a.lv.nlev && tid < kMaxSets) {
-        t.lvl[tid] = a.lv.lvl[tid];
-        t.M[tid] = a.lv.M[tid];
-        t.My[tid] = a.lv.My[tid];
-        t.off[tid] = a.lv.off[tid];
-        t.size[tid] = a.lv.size[tid];
-        t.woff[tid] = a.lv.woff[tid];
-    }
 }
 
 }  // namespace

@@ -139,6 +139,10 @@ int resident_slots(const void *kernel, int threads, size_t smem);
 hipError_t launch_coarsen(const CoarsenArgs &a, bool bf16, size_t smem_bytes, hipStream_t st);
 hipError_t launch_attend(const AttnArgs &a, bool bf16, int geometry, hipStream_t st);
 hipError_t launch_attend_bf16(const AttnArgs &a, int geometry, hipStream_t st);
+// bf16 attention on groups of 128 queries (attend_group.hip): whether a call
+// takes it, and the launch
+bool group_attends(const AttnArgs &a, bool two_d);
+hipError_t launch_attend_group(const AttnArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_lin_far(const AttnArgs &a, int geometry, hipStream_t st);
 hipError_t launch_lists(int two_d, int nblocks, int nby, int causal, const Levels &lv,
                         int32_t *out, hipStream_t st);

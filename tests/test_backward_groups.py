@@ -53,25 +53,32 @@ def row_group(ndim, r, n, nbx, nby, causal, g, wave, keys):
     return m
 
 
+def window_col(r, nby, m, cc):
+    if r == 8 and nby % 2 == 0:
+        c0 = m["cy"] & ~1
+        return c0 + cc if cc < 2 else c0 - 1 if cc == 2 and m["y0"] < c0 else c0 + 2
+    return m["y0"] + cc
+
+
 def tile_run(ndim, r, n, W, m, t, i):
     if ndim == 1:
         tok = m["lo"] + 64 * t + 8 * i
         return tok if tok + 8 <= n else n - 8
     if r == 8:
-        col, row = t // m["ncx"], t % m["ncx"]
-        return ((m["x0"] + row) * 8 + i) * W + (m["y0"] + col) * 8
+        col, row = window_col(r, W // 8, m, t // m["ncx"]), t % m["ncx"]
+        return ((m["x0"] + row) * 8 + i) * W + col * 8
     c, p0 = t >> 2, (t & 3) * 64 + 8 * i
     col, row = c // m["ncx"], c % m["ncx"]
     return ((m["x0"] + row) * 16 + (p0 >> 4)) * W + (m["y0"] + col) * 16 + (p0 & 15)
 
 
-def tile_used(ndim, r, m, t, hb):
+def tile_used(ndim, r, nby, m, t, hb):
     if not m["active"]:
         return False
     if ndim == 1:
         return m["wlo"] <= 64 * t + 32 * hb < m["whi"]
     if r == 8:
-        return abs(m["y0"] + t // m["ncx"] - m["cy"]) <= 1
+        return abs(window_col(r, nby, m, t // m["ncx"]) - m["cy"]) <= 1
     return True
 
 
@@ -112,7 +119,7 @@ def test_groups_cover_near_window(ndim, r, n, nbx, nby, causal, keys):
             got = []
             for t in range(m["ntile"]):
                 for hb in range(2):
-                    if tile_used(ndim, r, m, t, hb):
+                    if tile_used(ndim, r, nby, m, t, hb):
                         rows = [tile_run(ndim, r, n, W, m, t, 4 * hb + x // 8) + x % 8 for x in range(32)]
                         if causal and 64 * t + 32 * hb == m["wdiag"]:
                             assert rows == own
