@@ -77,31 +77,24 @@ struct TileMap {
     int qb, cx, cy;     // query block (1D) / cell (2D)
 };
 
-// Element offset of tile row `row` of tile `t`, or -1 for an empty slot.
-// *coarse tells whether the offset indexes the coarse arrays.
-template <int GEOM, int D>
-__device__ inline long long row_source(const AttnArgs &a, const LvTab &lt, const TileMap &m, int slice, int t,
-                                       int row, bool *coarse)
+// Source of tile row `row` of tile `t`: a near row's token from near0 (>= 0),
+// a coarse row of the slice as -2 - row, or -1 for an empty slot.
+template <int GEOM>
+__device__ inline int row_source(const AttnArgs &a, const LvTab &lt, const TileMap &m, int t, int row)
 {
     if (t < m.nnear) {
-        *coarse = false;
-        long long tok;
-        if constexpr (GEOM == GEOM_2D) {
-            const int pg = t * KT + row;   // position in the near cells' tokens, cell after cell
+        const int pg = t * KT + row;
+        if constexpr (GEOM == GEOM_2D) {   // position in the near cells' tokens, cell after cell
             const int ci = pg / m.csz;
             if (ci >= m.ncell) return -1;
-            const int wr = ci / m.wny;
-            const int ncx = m.wx0 + wr, ncy = m.wy0 + ci - wr * m.wny;
+            const int wr = ci / m.wny, wc = ci - wr * m.wny;
             const int p = pg - ci * m.csz;
             const int pa = p / a.r, pb = p - pa * a.r;
-            tok = (long long)(ncx * a.r + pa) * a.side + (ncy * a.r + pb);
+            return (wr * a.r + pa) * a.side + wc * a.r + pb;
         } else {
-            tok = m.klo + (long long)t * KT + row;
-            if (tok >= m.khi) return -1;
+            return m.klo + pg < m.khi ? pg : -1;
         }
-        return ((long long)slice * a.n + tok) * D;
     }
-    *coarse = true;
     // slot = level * slot_group + basis * K + j; slots past the bases of a
     // level (per-level padding) and past the list are empty
     const int kslot = (GEOM == GEOM_2D) ? kSlots2D : kSlots1D;
@@ -117,7 +110,7 @@ __device__ inline long long row_source(const AttnArgs &a, const LvTab &lt, const
     else
         g = list1d_entry(m.qb, lt.lvl[set], j, lt.M[set], a.causal);
     if (g < 0) return -1;
-    return ((long long)slice * a.R + lt.off[set] + g) * D;
+    return -2 - (lt.off[set] + g);
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -128,19 +121,29 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // coarse tile are formed once per workgroup, one slot per thread.
 // WIDE: per-level normalisation with levels of several 32-key blocks (2D,
 // rank p >= 2), the only plans that need the level accumulators.
-template <bool BF16, int NW, int GEOM, bool LIN, int D, bool WIDE>
-__global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
+// KS > 1 (joint normalisation, not FMA-linear): a workgroup takes 32 queries
+// of a block, and its key tiles are dealt to KS waves with LDS tiles of their
+// own, each with its own online softmax, merged at the end.  A grid that
+// leaves CUs idle is bound by one workgroup's chain of tiles: in fp32 8192
+// cycles of matrix instructions per tile, one wave on each SIMD, plus the
+// tile's loads.  1024 tokens of one head in blocks of 64: 39.2 us for whole
+// blocks (16 workgroups of two waves, four tiles each in turn), 18.4 us split.
+template <bool BF16, int NW, int GEOM, bool LIN, int D, bool WIDE, int KS = 1>
+__global__ __launch_bounds__(64 * NW * KS) void attend_kernel(AttnArgs a)
 {
+    static_assert(KS == 1 || (NW == 1 && !LIN && !WIDE), "split keys: joint normalisation only");
     constexpr int NT = 64 * NW;
     constexpr int ND = D / 32;                    // 32-channel blocks of O (accumulators)
     constexpr int KP = kRowPitch<BF16, D>;        // LDS pitch of K (and fp32 V) rows
     static_assert(D == 32 || D == 64 || D == 128, "head dim");
-    __shared__ TileSmem<BF16, D> sm;
+    __shared__ TileSmem<BF16, D> smem[KS];
     __shared__ LvTab lt;
     __shared__ float lin_q[LIN ? kMaxCoarse * D : 1];          // coarse query of each level
     __shared__ float lin_s[LIN ? KT : 1];                      // raw scores of a coarse tile's slots
 
-    const int tid = threadIdx.x;
+    const int ks = KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT) : 0;   // this wave's key group
+    const int tid = threadIdx.x - ks * NT;
+    TileSmem<BF16, D> &sm = smem[ks];
     const int lane = tid & 63, wave = tid >> 6;
     const int hh = lane >> 5, l32 = lane & 31;
 
@@ -161,6 +164,13 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
     if ((total & 7) == 0) {
         const int per = total >> 3;
         wg = (wg & 7) * per + (wg >> 3);
+    }
+    // KS > 1: workgroups of a block's 32-query pieces are neighbours
+    int piece = wave;
+    if constexpr (KS > 1) {
+        const int np = (a.qtile + 31) >> 5, w = wg / np;
+        piece = wg - w * np;
+        wg = w;
     }
     const int slice = wg / a.tiles_per_slice;
     const int qt = wg - slice * a.tiles_per_slice;
@@ -204,8 +214,8 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
 
     // This lane's query (lanes past a block smaller than the wave repeat one
     // of its queries and store nothing).
-    const bool qlive = wave * 32 + l32 < a.qtile;
-    const int ql = qlive ? wave * 32 + l32 : l32 % a.qtile;
+    const bool qlive = piece * 32 + l32 < a.qtile;
+    const int ql = qlive ? piece * 32 + l32 : l32 % a.qtile;
     long long qtok;
     if constexpr (GEOM == GEOM_2D) {
         const int pa = ql / a.r, pb = ql - pa * a.r;
@@ -215,7 +225,7 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
     }
     const long long qrow = ((long long)slice * a.n + qtok) * D;
     // largest query index of this wave (1D / dense), for skipping masked tiles
-    const long long wave_qmax = (long long)qt * a.qtile + wave * 32 + 31;
+    const long long wave_qmax = (long long)qt * a.qtile + piece * 32 + 31;
 
     // Q^T operand, resident for the whole tile loop.
     bf16x8 qb[BF16 ? D / 16 : 1];
@@ -242,54 +252,49 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
     int kval[KPER];
     uint4 vreg[VPER][BF16 ? 2 : 1];
 
-    const __bf16 *kb16 = nullptr;
+    // first near row (K and V) and the slice's coarse rows, in elements
+    long long near0 = (long long)slice * a.n;
+    if constexpr (GEOM == GEOM_2D)
+        near0 += (long long)m.wx0 * a.r * a.side + m.wy0 * a.r;
+    else
+        near0 += m.klo;
+    const long long coarse0 = (long long)slice * a.R;
+    constexpr int ROWBYTES = D * (BF16 ? 2 : 4);
+    static_assert(KT == 64, "one row's source per lane");
+    auto row_chunk = [&](const void *fine, const void *coarse, int src, int col) -> uint4 {
+        if (src >= 0)
+            return *reinterpret_cast<const uint4 *>(static_cast<const char *>(fine) + (near0 + src) * ROWBYTES + col * 16);
+        if (src < -1)
+            return *reinterpret_cast<const uint4 *>(static_cast<const char *>(coarse) + (coarse0 - 2 - src) * ROWBYTES +
+                                                    col * 16);
+        return make_uint4(0, 0, 0, 0);
+    };
+    // each lane works out the source of one row of the tile, and the loads take
+    // it from there (64 x 64 map of 8 heads in fp32: 101 us with the source and
+    // its divisions worked out for each load, 80 us so)
     auto fetch = [&](int t) {
+        const int mine = row_source<GEOM>(a, lt, m, t, lane);
 #pragma unroll
         for (int i = 0; i < KPER; ++i) {
             const int c = tid + i * NT;
+            const int row = c / KCOLS, col = c - row * KCOLS;
+            const int src = __shfl(mine, row);
             kreg[i] = make_uint4(0, 0, 0, 0);
-            kval[i] = 0;
-            if (c < KCHUNKS) {
-                const int row = c / KCOLS, col = c - row * KCOLS;
-                bool co;
-                const long long off = row_source<GEOM, D>(a, lt, m, slice, t, row, &co);
-                if (off >= 0) {
-                    const char *base = static_cast<const char *>(co ? a.kbar : a.k);
-                    kreg[i] = *reinterpret_cast<const uint4 *>(base + (off * (BF16 ? 2 : 4)) + col * 16);
-                    kval[i] = 1;
-                }
-            }
+            if (c < KCHUNKS) kreg[i] = row_chunk(a.k, a.kbar, src, col);
+            kval[i] = src != -1;
         }
 #pragma unroll
         for (int i = 0; i < VPER; ++i) {
             const int p = tid + i * NT;
+            const int kp = p / KCOLS, col = p - kp * KCOLS;
 #pragma unroll
-            for (int e = 0; e < (BF16 ? 2 : 1); ++e) vreg[i][e] = make_uint4(0, 0, 0, 0);
-            if (p < VTASKS) {
-                if constexpr (BF16) {
-                    const int kp = p / KCOLS, col = p - kp * KCOLS;
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        bool co;
-                        const long long off = row_source<GEOM, D>(a, lt, m, slice, t, 2 * kp + e, &co);
-                        if (off >= 0) {
-                            const char *base = static_cast<const char *>(co ? a.vbar : a.v);
-                            vreg[i][e] = *reinterpret_cast<const uint4 *>(base + off * 2 + col * 16);
-                        }
-                    }
-                } else {
-                    const int row = p / KCOLS, col = p - row * KCOLS;
-                    bool co;
-                    const long long off = row_source<GEOM, D>(a, lt, m, slice, t, row, &co);
-                    if (off >= 0) {
-                        const char *base = static_cast<const char *>(co ? a.vbar : a.v);
-                        vreg[i][0] = *reinterpret_cast<const uint4 *>(base + off * 4 + col * 16);
-                    }
-                }
+            for (int e = 0; e < (BF16 ? 2 : 1); ++e) {
+                const int src = __shfl(mine, BF16 ? 2 * kp + e : kp);
+                vreg[i][e] = make_uint4(0, 0, 0, 0);
+                if (p < VTASKS) vreg[i][e] = row_chunk(a.v, a.vbar, src, col);
             }
         }
     };
-    (void)kb16;
 
     auto stash = [&]() {
 #pragma unroll
@@ -398,12 +403,18 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
     for (int db = 0; db < (WIDE ? ND : 1); ++db) ol[db] = f32x16{0};
     float ml = -INFINITY, ll = 0.f;
 
-    fetch(0);
-    for (int t = 0; t < ntiles; ++t) {
+    // key group ks takes tiles ks, ks + KS, ..; every wave walks the same number
+    // of steps
+    // (with several groups a tile is usually a group's only one: no loads ahead)
+    if (KS == 1) fetch(0);
+    for (int t0 = 0; t0 < ntiles; t0 += KS) {
+        const int t = t0 + ks;
+        if (KS == 1 || t0 > 0) __syncthreads();
+        if (KS > 1 && t < ntiles) fetch(t);
+        if (KS == 1 || t < ntiles) stash();
         __syncthreads();
-        stash();
-        __syncthreads();
-        if (t + 1 < ntiles) fetch(t + 1);
+        if (KS > 1 && t >= ntiles) continue;
+        if (KS == 1 && t + 1 < ntiles) fetch(t + 1);
 
         const bool near_tile = t < m.nnear;
         long long key0 = 0;
@@ -561,6 +572,38 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
         for (int kb = 0; kb < 2; ++kb) pv_block(s[kb], kb, o);
     }
 
+    if constexpr (KS > 1) {
+        // merge the key groups' (m, l, O) in group order: groups 1 .. KS - 1
+        // leave theirs in their tile's LDS, [value][thread]
+        constexpr int NV = 16 * ND + 2;
+        static_assert(NV * NT * 4 <= (int)sizeof(TileSmem<BF16, D>), "merge buffer");
+        __syncthreads();   // the tiles are no longer read
+        if (ks > 0) {
+            float *const b = reinterpret_cast<float *>(&sm) + tid;
+            b[0] = mrun;
+            b[NT] = lrun;
+#pragma unroll
+            for (int db = 0; db < ND; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) b[(2 + 16 * db + i) * NT] = o[db][i];
+        }
+        __syncthreads();
+        if (ks > 0) return;
+#pragma unroll 1
+        for (int x = 1; x < KS; ++x) {
+            const float *const b = reinterpret_cast<const float *>(&smem[x]) + tid;
+            // (a group without a key of this query: m = -1e30, l = 0, O = 0)
+            const float mx = b[0], mnew = fmaxf(mrun, mx);
+            const float fa = fast_exp2(mrun - mnew), fb = fast_exp2(mx - mnew);
+            mrun = mnew;
+            lrun = lrun * fa + b[NT] * fb;
+#pragma unroll
+            for (int db = 0; db < ND; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[db][i] = o[db][i] * fa + b[(2 + 16 * db + i) * NT] * fb;
+        }
+    }
+
     // ----------------------------------------------------------- epilogue
     const float ltot = lrun + __shfl_xor(lrun, 32);
     const float inv = 1.0f / ltot;
@@ -582,12 +625,28 @@ __global__ __launch_bounds__(64 * NW) void attend_kernel(AttnArgs a)
     }
 }
 
+// Pieces of 32 queries up to which an fp32 call's keys are split over four
+// waves: one round of the 256 CUs, each holding one such workgroup (141 KB of
+// LDS at d = 64).  Blocks of 64, whole blocks -> split: 32 pieces 39.5 -> 18.6 us,
+// 256 pieces 39.6 -> 19.3 (causal 31.1 -> 19.0), blocks of 128, 64 pieces 59.4 ->
+// 29.1; past the line 512 pieces 38.4 -> 35.4 but causal 30.1 -> 35.3, 1024 pieces
+// 42.5 -> 67.9.
+constexpr unsigned kSplitPieces = 256;
+
 template <bool BF16, int GEOM, bool LIN, int D, bool WIDE>
 hipError_t launch_nw_w(const AttnArgs &a, hipStream_t st)
 {
     const unsigned grid = (unsigned)a.tiles_per_slice * (unsigned)a.nslice;
     if (a.qtile <= 0 || a.qtile > 256 || (a.qtile > 32 && a.qtile % 32)) return hipErrorInvalidValue;
-    switch ((a.qtile + 31) / 32) {
+    const unsigned chunks = (unsigned)(a.qtile + 31) / 32;
+    // (d = 128: four tiles do not fit the LDS; 3, 5 and 7 waves: refused below)
+    if constexpr (!BF16 && !LIN && !WIDE && GEOM != GEOM_DENSE && D <= 64) {
+        if (!a.norm_level && grid <= kSplitPieces / chunks && chunks != 3 && chunks != 5 && chunks != 7) {
+            hipLaunchKernelGGL((attend_kernel<false, 1, GEOM, false, D, false, 4>), dim3(grid * chunks), dim3(256), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    switch (chunks) {
     case 1: hipLaunchKernelGGL((attend_kernel<BF16, 1, GEOM, LIN, D, WIDE>), dim3(grid), dim3(64), 0, st, a); break;
     case 2: hipLaunchKernelGGL((attend_kernel<BF16, 2, GEOM, LIN, D, WIDE>), dim3(grid), dim3(128), 0, st, a); break;
     case 4: hipLaunchKernelGGL((attend_kernel<BF16, 4, GEOM, LIN, D, WIDE>), dim3(grid), dim3(256), 0, st, a); break;
