@@ -205,25 +205,16 @@ bool choose_stream_1d(fma_plan_s *p)
         }
     }
     if (best_d == 0) return false;
-    // The widest unit that still gives every resident wave one.  With more than
-    // 16 sets the waves' own work (two column groups of weights split per step)
-    // bounds the pass, not HBM, and a round of units that leaves waves idle
-    // costs its share: there the widest that keeps nine tenths of the rounds'
-    // waves busy, if any does (96 slices x 16384 tokens, 24 sets: units of 1024,
-    // 1.5 rounds, 126 us; of 512, three rounds, 105 us, and 4 us more in
-    // coarsen_finish.  With 6 sets no difference: 72.7 us either way).
-    const long long resident = 256 * 4 * best_wgs;
-    long long cw = 0, balanced = 0;
+    // the widest unit that still gives every resident wave one
+    long long cw = p->r;
     for (int k = 3; k >= 0; --k) {
         const long long c = (long long)p->r << k;
         if (c > 1024) continue;
-        const long long units = 2LL * p->nslice * cdiv(p->n, c);
-        if (units < resident) continue;
-        if (cw == 0) cw = c;
-        if (balanced == 0 && 10 * units >= 9 * cdiv(units, resident) * resident) balanced = c;
+        if (2LL * p->nslice * cdiv(p->n, c) >= 256 * 4 * best_wgs) {
+            cw = c;
+            break;
+        }
     }
-    if (nwd > 4 && balanced > 0) cw = balanced;
-    if (cw == 0) cw = p->r;
     p->chunk = (int)cw;
     p->depth = best_d;
     p->wave_lds = (int)best_lds;
