@@ -387,11 +387,12 @@ hipError_t launch_g(const AttnArgs &a, bool two_d, hipStream_t st)
 
 // What the groups can run: blocks that they cut into whole 32-query chunks (1D
 // multiples of 32, 2D cells of 8 x 8 and 16 x 16), lists that fit the group's
-// table, and under the per-level normalisation levels that fit a 32-slot piece.
+// table, and under the per-level normalisation levels that fit a 32-slot piece
+// (a plan without a coarse level has none, whatever its slots per level).
 static bool group_fits(const AttnArgs &a, bool two_d)
 {
     if (a.n > 0x7fffffffLL - 4096 || a.qbar) return false;
-    if (a.norm_level && a.slot_group > 32) return false;
+    if (a.norm_level && a.nslot > 0 && a.slot_group > 32) return false;
     if (!two_d) return a.r % 32 == 0 && group_lists_fit<GEOM_1D>(a);
     return a.r == 8 ? group_lists_fit<GEOM_2DP>(a) : a.r == 16 && group_lists_fit<GEOM_2D>(a);
 }
