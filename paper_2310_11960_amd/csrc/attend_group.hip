@@ -187,6 +187,8 @@ void attend_group_kernel(AttnArgs a)
     }
 
     const float cs = a.scale_log2;
+    // a masked score: -inf once scaled (the scale may be negative)
+    const float off = !SQ && cs < 0.f ? INFINITY : -INFINITY;
     if constexpr (SQ) {
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -235,10 +237,10 @@ void attend_group_kernel(AttnArgs a)
         auto mask_rows = [&](f32x16 &x) {
             if (mode == 1) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = grow(i, hh) <= l32 ? x[i] : -INFINITY;
+                for (int i = 0; i < 16; ++i) x[i] = grow(i, hh) <= l32 ? x[i] : off;
             } else if (mode == 2) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = (mw >> (8 * (i >> 2) + (i & 3))) & 1u ? x[i] : -INFINITY;
+                for (int i = 0; i < 16; ++i) x[i] = (mw >> (8 * (i >> 2) + (i & 3))) & 1u ? x[i] : off;
             }
         };
         mask_rows(s);
