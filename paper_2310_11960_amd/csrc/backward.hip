@@ -361,6 +361,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
     }
     const float dq_row = psum(dpart);
     const float cs = a.scale_log2;
+    const float off = cs < 0.f ? INFINITY : -INFINITY;   // a masked score: -inf once scaled
     // 1D: the last query of the workgroup; causal near tiles past it add nothing
     const long long wg_qmax = TWO_D ? 0 : (long long)b * a.r + (long long)(gi * NW + NW) * 32 - 1;
     // number of tiles this workgroup walks (causal: the near tiles up to its queries)
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                 // every row of the block visible to every query of the wave?
                 const bool allvis =
                     __builtin_amdgcn_ballot_w64(!(full && (!causal || qrel >= kb * 32 + 31))) == 0;
-                // masked rows' raw scores to -inf (branch-free: every row's
+                // masked rows' raw scores to what the scale makes -inf (branch-free: every row's
                 // validity read, four rows per load)
                 auto mask_rows = [&](f32x16 &x) {
                     if (allvis) return;
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                         for (int e = 0; e < 4; ++e) {
                             const int i = 4 * c + e;
                             const bool ok = (full || vl[e] != 0) && (!causal || r0 + e <= qrel);
-                            x[i] = ok ? x[i] : -INFINITY;
+                            x[i] = ok ? x[i] : off;
                         }
                     }
                 };

@@ -91,6 +91,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     build_lists<GEOM>(a, m, gl, grp, sm.st, nct * KT, wave, lane, sm.list);
 
     const float cs = a.scale_log2;
+    const float off = cs < 0.f ? INFINITY : -INFINITY;   // a masked score: -inf once scaled
     const RowOff ro = row_offsets(l32, hh);
     const TrOff to = tr_offsets(lane);
     f32x16 dq0 = {0}, dq1 = {0};
@@ -112,19 +113,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         auto mask_rows = [&](f32x16 &x) {
             if (mode == 1) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = acc_row(i, hh) <= l32 ? x[i] : -INFINITY;
+                for (int i = 0; i < 16; ++i) x[i] = acc_row(i, hh) <= l32 ? x[i] : off;
             } else if (mode == 2) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = (mw >> (8 * (i >> 2) + (i & 3))) & 1u ? x[i] : -INFINITY;
+                for (int i = 0; i < 16; ++i) x[i] = (mw >> (8 * (i >> 2) + (i & 3))) & 1u ? x[i] : off;
             }
         };
         mask_rows(s);
         if (first) {
             // a near piece: every query sees at least one of its rows
-            float mx = s[0];
+            float mx = s[0] * cs;
 #pragma unroll
-            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-            mrun = pmax(mx) * cs;
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i] * cs);
+            mrun = pmax(mx);
             first = false;
         }
         // P against the reference maximum as it stands (it only keeps P
