@@ -15,9 +15,9 @@
 // 128, else 64) by direct-to-LDS loads, one barrier per tile; a wave takes the
 // 32-row pieces of its own block's window and list.  Per piece:
 //   S^T = K Q^T (ds_read_b128 rows, Q in registers), P = exp2(c s - m), l the
-//   fp32 sum of the bf16 P, O^T += V^T P^T (transposing LDS reads).  m is the
-//   running maximum, or (SQ) the first piece's, raised only when a lane's
-//   weights would pass 2^64.
+//   fp32 sum of P (SQ: of the bf16 P), O^T += V^T P^T (transposing LDS reads).
+//   m is the running maximum, or (SQ) the first piece's, raised only when a
+//   lane's weights would pass 2^64.
 // Each row's 16-byte chunk c sits at chunk c ^ swzd(row).
 #include "level_weights.hpp"
 #include "row_groups.hpp"
@@ -90,13 +90,14 @@ __device__ inline void store32(const f32x16 &o, float inv, __bf16 *r0, __bf16 *r
 }
 
 // PL: printed per-level normalisation (levels inside a 32-slot piece).
-// SQ (scaled queries): c Q rounded to bf16 and no running maximum, the
-// arithmetic of attend_mfma.hip, for the block sizes both kernels take (d = 64,
-// blocks of 64 and more), so that a plan's results do not depend on which
-// runs.  The others keep the fp32 scale and the running maximum of attend.hip,
-// under which a dominating source's weight is exactly 1: without it the error
-// against float64 was 4 % larger (2.24e-3 against 2.14e-3), for 122 instead of
-// 154 us at d = 128.
+// SQ (scaled queries): c Q rounded to bf16, no running maximum and l from the
+// bf16 weights, as attend_mfma.hip has them, for the block sizes both kernels
+// take (d = 64, blocks of 64 and more).  The two still differ by rounding: that
+// kernel subtracts m inside the matrix product and checks 16 rows at a time.
+// The others keep the fp32 scale, the running maximum and the fp32 row sum of
+// attend.hip; under the running maximum a dominating source's weight is exactly
+// 1: without it the error against float64 was 4 % larger (2.24e-3 against
+// 2.14e-3), for 122 instead of 154 us at d = 128.
 template <int D, int GEOM, bool PL, bool SQ>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : PL || !SQ ? 3 : 4)))
 void attend_group_kernel(AttnArgs a)
@@ -245,9 +246,7 @@ void attend_group_kernel(AttnArgs a)
         };
         mask_rows(s);
         // the weights against m as it stands (it only keeps them finite) and
-        // their sum
-        // (l from the rounded weights, so that a row that one source dominates
-        // normalises it exactly)
+        // their sum: of the fp32 weights, or (SQ) of their bf16 roundings
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
         const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
         uint32_t w[8];
@@ -257,8 +256,12 @@ void attend_group_kernel(AttnArgs a)
             for (int x = 0; x < 8; ++x) {
                 const float x0 = SQ ? s[2 * x] - mrun : fmaf(s[2 * x], cs, -mrun);
                 const float x1 = SQ ? s[2 * x + 1] - mrun : fmaf(s[2 * x + 1], cs, -mrun);
-                w[x] = pack2(gexp2(x0), gexp2(x1));
-                bl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[x]), ones, bl, false);
+                const float p0 = gexp2(x0), p1 = gexp2(x1);
+                w[x] = pack2(p0, p1);
+                if constexpr (SQ)
+                    bl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[x]), ones, bl, false);
+                else
+                    bl += p0 + p1;
             }
             return bl;
         };
