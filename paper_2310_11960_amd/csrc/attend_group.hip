@@ -141,7 +141,7 @@ void attend_group_kernel(AttnArgs a)
             const int ch = 16 * (lp ^ swzd<D>(row));
             const uint32_t kd = lds_u32(sm.k[st]) + i * 1024, vd = lds_u32(sm.v[st]) + i * 1024;
             if (co) {
-                const int x = sm.list.crow[(t - nnear) * TR + row];   // empty rows read coarse row 0 (weight 0)
+                const int x = sm.list.crow[(t - nnear) * TR + row];   // (a piece without rows, which no wave takes: row 0)
                 const long long r = (long long)(x < 0 ? 0 : x) * RB + ch;
                 dma16(kb + r, kd);
                 dma16(vb + r, vd);
@@ -326,12 +326,14 @@ void attend_group_kernel(AttnArgs a)
             } else {
                 const int pc = PPT * (t - nnear) + hb;
                 if (!m.active || pc < gl.pc0 || pc >= gl.pc0 + gl.npc) continue;
-                mw = sm.list.vis[GEOM == GEOM_2DP && !PL ? wave >> 1 : 0][pc] >> (4 * hh);
+                if (PL && pc == gl.pc0) lnear = pair_sum(lrun);   // the near field's row sum, final by now
+                mw = __builtin_amdgcn_readfirstlane(sm.list.vis[GEOM == GEOM_2DP && !PL ? wave >> 1 : 0][pc]);
+                if (mw == 0) continue;
+                mw >>= 4 * hh;
                 mode = 2;
                 if constexpr (PL) {
                     // every level of the piece normalised on its own and
-                    // weighted by the near field's row sum (final by now)
-                    if (pc == gl.pc0) lnear = pair_sum(lrun);
+                    // weighted by the near field's row sum
                     f32x16 s = scores(kt);
 #pragma unroll
                     for (int i = 0; i < 16; ++i)

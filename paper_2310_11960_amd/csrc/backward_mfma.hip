@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
                 dma16(kg + o, kd);
                 dma16(vg + o, vd);
             } else {
-                // gathered rows; empty ones read coarse row 0 (their weight is 0)
+                // gathered rows (a piece without rows, which no wave takes: row 0)
                 const int row = sm.list.crow[(t - nnear) * KT + 8 * i + (lane >> 3)];
                 const long long o = (long long)(row < 0 ? 0 : row) * ROWB + loff - (lane >> 3) * ROWB;
                 dma16(kb + o, kd);
@@ -187,7 +187,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             } else {
                 const int pc = 2 * (t - nnear) + hb;
                 if (!m.active || pc < gl.pc0 || pc >= gl.pc0 + gl.npc) continue;
-                mw = sm.list.vis[GEOM == GEOM_2DP ? wave >> 1 : 0][pc] >> (4 * hh);
+                mw = __builtin_amdgcn_readfirstlane(sm.list.vis[GEOM == GEOM_2DP ? wave >> 1 : 0][pc]);
+                if (mw == 0) continue;
+                mw >>= 4 * hh;
                 mode = 2;
             }
             piece(kt, vt, mode, mw);

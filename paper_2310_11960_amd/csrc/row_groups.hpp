@@ -240,8 +240,12 @@ struct GroupLists {
     int b0, nb;           // 1D: first block of the group, blocks
 };
 
+// An empty row of a piece that has others repeats one of them: its weight is
+// 0, and what it loads is a row that the queries see anyway, so that a coarse
+// row that is not finite reaches no query that does not list it (0 * inf is
+// NaN).  Pieces without a row the kernels skip.
 struct ListSmem {
-    int crow[kGroupRows];             // coarse row of every list row (-1: empty)
+    int crow[kGroupRows];             // coarse row of every list row (-1: a piece without rows)
     uint32_t vis[2][kGroupRows / 32]; // rows each cell of a 2D pair sees (else [0])
 };
 
@@ -319,7 +323,9 @@ __device__ __attribute__((always_inline)) inline void build_lists(const A &a, co
                 }
             }
         }
-        ls.crow[e] = row;
+        const uint32_t on32 = (uint32_t)(__builtin_amdgcn_ballot_w64(row >= 0) >> (lane & 32));
+        const int sub = __shfl(row, (lane & 32) + (on32 ? __builtin_ctz(on32) : 0));
+        ls.crow[e] = row < 0 ? sub : row;
 #pragma unroll
         for (int c = 0; c < (GEOM == GEOM_2DP ? 2 : 1); ++c) {
             const unsigned long long b = __builtin_amdgcn_ballot_w64((mask >> c) & 1);
