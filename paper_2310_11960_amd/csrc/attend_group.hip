@@ -1,7 +1,7 @@
 // attend_group.hip -- fused multilevel FMA attention for bf16 on groups of 128
 // queries (row_groups.hpp): any block of a multiple of 32 tokens, 2D cells of
 // 8 x 8 and 16 x 16, head dims 32, 64 and 128, either normalisation
-// (group_attends tells where it is taken).
+// (attend_route.hpp tells where it is taken).
 //
 // What bounds it: at 1D 65536 x 128, 32 slices, its loads and stores alone take
 // 181 us (1.08 GB at 6 TB/s) and its arithmetic alone 250-295 us, the sum of
@@ -19,8 +19,8 @@
 //   m is the running maximum, or (SQ) the first piece's, raised only when a
 //   lane's weights would pass 2^64.
 // Each row's 16-byte chunk c sits at chunk c ^ swzd(row).
+#include "attend_route.hpp"
 #include "level_weights.hpp"
-#include "row_groups.hpp"
 
 namespace fma_dev {
 
@@ -392,40 +392,10 @@ hipError_t launch_g(const AttnArgs &a, bool two_d, hipStream_t st)
 
 }  // namespace
 
-// What the groups can run: blocks that they cut into whole 32-query chunks (1D
-// multiples of 32, 2D cells of 8 x 8 and 16 x 16), lists that fit the group's
-// table, and under the per-level normalisation levels that fit a 32-slot piece
-// (a plan without a coarse level has none, whatever its slots per level).
-static bool group_fits(const AttnArgs &a, bool two_d)
-{
-    if (a.n > 0x7fffffffLL - 4096 || a.qbar) return false;
-    if (a.norm_level && a.nslot > 0 && a.slot_group > 32) return false;
-    if (!two_d) return a.r % 32 == 0 && group_lists_fit<GEOM_1D>(a);
-    return a.r == 8 ? group_lists_fit<GEOM_2DP>(a) : a.r == 16 && group_lists_fit<GEOM_2D>(a);
-}
-
-// Where they are the faster kernel.  Head dims 32 and 128 and blocks of 32:
-// against the register-staged kernel (d = 128 causal 7808 x 128, 64 slices:
-// 581 -> 154 us; blocks of 32, 64 slices of 4000: 207 -> 41 us).  d = 64,
-// against the fixed-shape stream (attend_mfma.hip): every 2D map (128 x 128 at
-// 32 slices 163 -> 141 us, 16 x 16 cells 418 -> 322, 120 x 168 per level 272 ->
-// 233), 1D blocks of 64 (48 slices of 16384: 150 -> 111 us, causal 128 -> 89)
-// and 192 (214 -> 185, causal 169 -> 126).  Blocks of 128 and 256 fill that
-// kernel's workgroups exactly and its persistent stream hides each block's
-// start; it stays for bidirectional ones (65536 x 128, 16 slices: 175 us
-// against 180) and blocks of 256 (261 against 287) where the groups need several
-// rounds on the device.  Causal blocks of 128, half of whose near tiles are
-// partly masked, take groups (48 slices of 16384: 108 -> 102 us), and so does
-// whatever fits one round (8 slices of 4096: 11.5 -> 11.1 us, blocks of 256
-// causal 18.4 -> 15.9), except bidirectional blocks of 192, whose groups
-// straddle blocks without filling the device (19.1 us against 20.3).
 bool group_attends(const AttnArgs &a, bool two_d)
 {
-    if (!group_fits(a, two_d)) return false;
-    if (two_d || a.head_dim != kHeadDim || a.r < 128 || (a.causal && a.r < 256)) return true;
-    const int slots = resident_slots(reinterpret_cast<const void *>(&attend_group_kernel<64, GEOM_1D, false, true>), 256, 0);
-    const bool one_round = (long long)a.nslice * row_groups<GEOM_1D>(a) <= slots;
-    return a.r % 128 ? !one_round : one_round;
+    const unsigned k = attend_kernels(a, two_d);
+    return k == ATTEND_GROUPS || (k == (ATTEND_GROUPS | ATTEND_STREAM) && groups_win(a, compute_units()));
 }
 
 hipError_t launch_attend_group(const AttnArgs &a, bool two_d, hipStream_t st)

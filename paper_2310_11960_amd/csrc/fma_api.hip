@@ -15,6 +15,14 @@
 
 using fma_dev::Levels;
 
+int fma_dev::compute_units()
+{
+    int dev = -1, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return cus;
+}
+
 // Occupancy cache behind fma_dev::resident_slots: a small table guarded by a
 // mutex; an entry is added only after a successful query.
 int fma_dev::resident_slots(const void *kernel, int threads, size_t smem)

@@ -135,6 +135,8 @@ enum Geometry { GEOM_1D = 0, GEOM_2D = 1, GEOM_DENSE = 2, GEOM_2DP = 3 /* 2D, ce
 // per (device, kernel, threads, LDS) and kept; thread-safe.  0 on failure
 // (nothing is kept then).
 int resident_slots(const void *kernel, int threads, size_t smem);
+// CUs of the current device (0 on failure).
+int compute_units();
 
 hipError_t launch_coarsen(const CoarsenArgs &a, bool bf16, size_t smem_bytes, hipStream_t st);
 hipError_t launch_attend(const AttnArgs &a, bool bf16, int geometry, hipStream_t st);
