@@ -1884,7 +1884,10 @@ hipError_t launch_all(const BwdArgs &a0, hipStream_t st)
     const int cpb = (a.qtile + 31) / 32;   // 32-query chunks per block (a block below 32 is one)
     a.npart = a.nblocks * ((cpb + NW - 1) / NW);   // (query block, workgroup) rows per slice
     if (a.pslices <= 0) return hipErrorInvalidValue;
-    a.split_rows = BF16 && bwd_streams(a, TWO_D);
+    const bool streams = BF16 && backward_streams(a.n, a.R, a.r, TWO_D);
+    a.split_rows = streams;
+    // partial rows are laid out by sibling groups exactly where the streamed query pass writes them
+    if ((a.ngrp > 0) != (streams && !PL && !LIN && a.lv.nlev > 0)) return hipErrorInvalidValue;
     if (a.ngrp == 0 && (long long)2 * a.pslices * a.npart * a.nslot * kHeadDim > a.part_elems && a.lv.nlev > 0)
         return hipErrorInvalidValue;
     if (LIN && a.lv.nlev > 0 &&
@@ -1897,7 +1900,6 @@ hipError_t launch_all(const BwdArgs &a0, hipStream_t st)
     const int runs = (int)runs_ll;
     hipError_t e = hipSuccess;
     const long long per_slice = (long long)a.nblocks * ((cpb + NW - 1) / NW);   // query-pass workgroups
-    const bool streams = BF16 && bwd_streams(a, TWO_D);
     if (streams && !PL && !LIN) {
         if ((e = launch_bwd_query(a, TWO_D, st)) != hipSuccess) return e;
     } else if constexpr (BF16 && NW == 4 && !PL && !LIN) {

@@ -776,27 +776,16 @@ hipError_t launch_query(const BwdArgs &a, hipStream_t st)
 
 }  // namespace
 
-// Blocks that the 128-row groups cut into whole 32-row chunks: every 1D block
-// of a multiple of 32 and 2D cells of 8 x 8 and 16 x 16.  Blocks of 16 and
-// 4 x 4 cells (half a chunk) stay on the register-staged kernels, which pack
-// them with idle lanes.
-bool bwd_streams(const BwdArgs &a, bool two_d)
-{
-    // 32-bit tokens and coarse-row element offsets
-    if (a.n > 0x7fffffffLL - 4096 || (long long)a.R * kHeadDim > 0x7fffffffLL) return false;
-    return two_d ? a.r == 8 || a.r == 16 : a.r % 32 == 0;
-}
-
 hipError_t launch_bwd_query(const BwdArgs &a, bool two_d, hipStream_t st)
 {
-    if (!bwd_streams(a, two_d)) return hipErrorInvalidValue;
+    if (!backward_streams(a.n, a.R, a.r, two_d)) return hipErrorInvalidValue;
     if (!two_d) return launch_query<GEOM_1D>(a, st);
     return a.r == 8 ? launch_query<GEOM_2DP>(a, st) : launch_query<GEOM_2D>(a, st);
 }
 
 hipError_t launch_bwd_key(const BwdArgs &a, bool two_d, hipStream_t st)
 {
-    if (!bwd_streams(a, two_d)) return hipErrorInvalidValue;
+    if (!backward_streams(a.n, a.R, a.r, two_d)) return hipErrorInvalidValue;
     if (!two_d) return launch_key<GEOM_1D>(a, st);
     return a.r == 8 ? launch_key<GEOM_2DP>(a, st) : launch_key<GEOM_2D>(a, st);
 }

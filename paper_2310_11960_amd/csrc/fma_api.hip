@@ -508,9 +508,9 @@ fma_status_t fma_plan(const fma_desc_t *d, fma_plan_t *out)
         // gradients' line sums reuse the space
         size_t per_slice = nlev > 0 ? (size_t)2 * p.npart_max * p.nslot * fma_dev::kHeadDim : 0;
         // bf16 plans under the joint normalisation on streamed 128-row groups
-        // (see bwd_streams): one partial row per sibling group and slot
+        // (backward_streams): one partial row per sibling group and slot
         if (nlev > 0 && d->dtype == FMA_BF16 && !p.norm_level && !p.linear &&
-            (d->ndim == 1 ? p.r % 32 == 0 : p.r >= 8)) {
+            fma_dev::backward_streams(p.n, p.R, p.r, d->ndim == 2)) {
             p.bw_ngrp = d->ndim == 1 ? (int)cdiv(p.nblocks, 2) : (int)(cdiv(p.nbx, 2) * cdiv(p.nby, 2));
             p.bw_gslot = fma_dev::group_slots(d->ndim == 2, rank, nlev);
             per_slice = (size_t)2 * p.bw_ngrp * p.bw_gslot * fma_dev::kHeadDim;

@@ -128,6 +128,16 @@ __host__ __device__ constexpr int group_slots(int two_d, int rank, int nlev)
     return rank * group_window(two_d) + (nlev - rank) * (two_d ? kSlots2D : kSlots1D);
 }
 
+// Whether the bf16 backward of a plan runs on streamed 128-row groups: blocks
+// that they cut into whole 32-row chunks, every 1D block of a multiple of 32
+// and 2D cells of 8 x 8 and 16 x 16, with 32-bit tokens and coarse-row element
+// offsets.  Blocks of 16 and 4 x 4 cells (half a chunk) stay on the
+// register-staged kernels, which pack them with idle lanes.
+__host__ __device__ constexpr bool backward_streams(long long n, long long R, int r, int two_d)
+{
+    return n <= 0x7fffffffLL - 4096 && R * kHeadDim <= 0x7fffffffLL && (two_d ? r == 8 || r == 16 : r % 32 == 0);
+}
+
 enum Geometry { GEOM_1D = 0, GEOM_2D = 1, GEOM_DENSE = 2, GEOM_2DP = 3 /* 2D, cells in pairs (bf16 kernel) */ };
 
 // Resident workgroups of `kernel` (threads per workgroup, dynamic LDS bytes)
@@ -149,10 +159,9 @@ hipError_t launch_lin_far(const AttnArgs &a, int geometry, hipStream_t st);
 hipError_t launch_lists(int two_d, int nblocks, int nby, int causal, const Levels &lv,
                         int32_t *out, hipStream_t st);
 hipError_t launch_backward(const BwdArgs &a, bool bf16, bool two_d, hipStream_t st);
-// bf16 backward on streamed 128-row groups (backward_mfma.hip): whether a
-// plan's blocks take it; the query pass with the coarse rows' gradients (joint
+// bf16 backward on streamed 128-row groups (backward_mfma.hip, where
+// backward_streams): the query pass with the coarse rows' gradients (joint
 // normalisation, a.ngrp > 0) and the key pass
-bool bwd_streams(const BwdArgs &a, bool two_d);
 hipError_t launch_bwd_query(const BwdArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_bwd_key(const BwdArgs &a, bool two_d, hipStream_t st);
 hipError_t launch_stream_ref(const void *src, long long nwords, void *dst, long long ndst, int write_every,

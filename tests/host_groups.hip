@@ -52,6 +52,26 @@ extern "C" {
 
 unsigned host_attend_kernels(const int64_t *plan) { return attend_kernels(args_of(plan), plan[13] == 2); }
 
+// launch_backward on arguments whose sibling groups say that the bf16 streamed
+// query pass runs: its status.  tokens: per slice; launches nothing where the
+// blocks do not stream.
+int host_backward_status(int64_t tokens, int ngrp)
+{
+    BwdArgs a;
+    memset(&a, 0, sizeof(a));
+    a.n = tokens;
+    a.r = a.qtile = 64;
+    a.nslice = a.heads = a.heads_w = a.pslices = a.rank = 1;
+    a.nblocks = a.nbx = (int)(tokens / 64);
+    a.nby = 1;
+    a.ngrp = ngrp;
+    a.gslot = 6;
+    a.nslot = 3;
+    a.R = 4;
+    a.lv.nlev = 1;
+    return (int)launch_backward(a, true, false, nullptr);
+}
+
 int host_groups_win(const int64_t *plan, int cus) { return groups_win(args_of(plan), cus); }
 
 }  // extern "C"

@@ -22,7 +22,8 @@ def library():
         cmd = [HIPCC, "-O1", "-std=c++17", "-fPIC", "-shared", "--cuda-host-only", "--offload-arch=gfx950",
                "-Wno-unused-function", "-I", os.path.join(ROOT, "include"),
                "-I", os.path.join(ROOT, "paper_2310_11960_amd", "csrc"),
-               os.path.join(ROOT, "tests", "host_groups.hip"), "-o", so]
+               os.path.join(ROOT, "tests", "host_groups.hip"), "-Xlinker", F.library()._name, "-o", so,
+               "-Wl,-rpath," + os.path.dirname(F.library()._name)]
         r = subprocess.run(cmd, capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-3000:]
         return ctypes.CDLL(so)
