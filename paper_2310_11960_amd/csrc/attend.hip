@@ -646,8 +646,14 @@ hipError_t launch_nw_w(const AttnArgs &a, hipStream_t st)
             return hipGetLastError();
         }
     }
-    switch (chunks) {
-    case 1: hipLaunchKernelGGL((attend_kernel<BF16, 1, GEOM, LIN, D, WIDE>), dim3(grid), dim3(64), 0, st, a); break;
+    if (chunks == 1) {
+        hipLaunchKernelGGL((attend_kernel<BF16, 1, GEOM, LIN, D, WIDE>), dim3(grid), dim3(64), 0, st, a);
+        return hipGetLastError();
+    }
+    // bf16 blocks of more than one chunk: d = 64 and 1D without coarse queries
+    // never come here (attend_route.hpp)
+    if constexpr (BF16 && (D == kHeadDim || (GEOM == GEOM_1D && !LIN))) return hipErrorInvalidValue;
+    else switch (chunks) {
     case 2: hipLaunchKernelGGL((attend_kernel<BF16, 2, GEOM, LIN, D, WIDE>), dim3(grid), dim3(128), 0, st, a); break;
     case 4: hipLaunchKernelGGL((attend_kernel<BF16, 4, GEOM, LIN, D, WIDE>), dim3(grid), dim3(256), 0, st, a); break;
     case 6: hipLaunchKernelGGL((attend_kernel<BF16, 6, GEOM, LIN, D, WIDE>), dim3(grid), dim3(384), 0, st, a); break;

@@ -56,39 +56,6 @@ struct GroupSmem {
 __device__ inline float gexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ inline int grow(int i, int hh) { return 8 * (i >> 2) + 4 * hh + (i & 3); }   // accumulator row
 
-__device__ inline uint32_t pack2(float lo, float hi)
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 p = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
-    return __builtin_bit_cast(uint32_t, p);
-}
-
-// One 32-channel accumulator (rows channels, columns queries; scaled by inv) to
-// bf16: row l16 of the wave at r0, row 16 + l16 at r1 (this lane's 16-byte
-// chunk of 64 contiguous bytes; see store_rows in bwd_tiles.hpp).
-__device__ inline void store32(const f32x16 &o, float inv, __bf16 *r0, __bf16 *r1)
-{
-    uint32_t u[8];
-#pragma unroll
-    for (int x = 0; x < 8; ++x) u[x] = pack2(o[2 * x] * inv, o[2 * x + 1] * inv);
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const auto r = __builtin_amdgcn_permlane32_swap(u[4 * x + k], u[4 * x + 2 + k], false, false);
-            u[4 * x + k] = r[0];
-            u[4 * x + 2 + k] = r[1];
-        }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const auto r = __builtin_amdgcn_permlane16_swap(u[k], u[4 + k], false, false);
-        u[k] = r[0];
-        u[4 + k] = r[1];
-    }
-    *reinterpret_cast<uint4 *>(r0) = make_uint4(u[0], u[1], u[2], u[3]);
-    *reinterpret_cast<uint4 *>(r1) = make_uint4(u[4], u[5], u[6], u[7]);
-}
-
 // PL: printed per-level normalisation (levels inside a 32-slot piece).
 // SQ (scaled queries): c Q rounded to bf16, no running maximum and l from the
 // bf16 weights, as attend_mfma.hip has them, for the block sizes both kernels
@@ -257,7 +224,7 @@ void attend_group_kernel(AttnArgs a)
                 const float x0 = SQ ? s[2 * x] - mrun : fmaf(s[2 * x], cs, -mrun);
                 const float x1 = SQ ? s[2 * x + 1] - mrun : fmaf(s[2 * x + 1], cs, -mrun);
                 const float p0 = gexp2(x0), p1 = gexp2(x1);
-                w[x] = pack2(p0, p1);
+                w[x] = pack_bf16(p0, p1);
                 if constexpr (SQ)
                     bl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[x]), ones, bl, false);
                 else
@@ -341,7 +308,7 @@ void attend_group_kernel(AttnArgs a)
                     level_weights(s, lnear, a.slot_group);
                     uint32_t w[8];
 #pragma unroll
-                    for (int x = 0; x < 8; ++x) w[x] = pack2(s[2 * x], s[2 * x + 1]);
+                    for (int x = 0; x < 8; ++x) w[x] = pack_bf16(s[2 * x], s[2 * x + 1]);
                     pv(w, vt);
                     continue;
                 }
@@ -351,12 +318,12 @@ void attend_group_kernel(AttnArgs a)
     }
     if (!m.active) return;
     const float inv = 1.0f / pair_sum(lrun);
-    const int l16 = lane & 15, chunk = 2 * ((lane >> 4) & 1) + hh;
-    __bf16 *const ob = static_cast<__bf16 *>(a.out) + (long long)slice * a.n * D + 8 * chunk;
+    const int l16 = lane & 15;
+    __bf16 *const ob = static_cast<__bf16 *>(a.out) + (long long)slice * a.n * D + 8 * store_chunk(lane);
     __bf16 *const r0 = ob + wave_token<GEOM>(a, m, m.pos0 + l16) * D;
     __bf16 *const r1 = ob + wave_token<GEOM>(a, m, m.pos0 + 16 + l16) * D;
 #pragma unroll
-    for (int db = 0; db < ND; ++db) store32(o[db], inv, r0 + 32 * db, r1 + 32 * db);
+    for (int db = 0; db < ND; ++db) store_rows32(o[db], inv, r0 + 32 * db, r1 + 32 * db);
 }
 
 template <int D, int GEOM>

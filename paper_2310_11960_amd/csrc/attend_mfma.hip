@@ -2,7 +2,7 @@
 // (Eq. fma1d / Eq. fma2d under one softmax per query): a persistent stream for
 // 1D blocks that fill whole workgroups, FMA-linear, per-level maps of rank 2 and
 // more, and the dense reference; the other plans run on attend_group.hip
-// (group_attends).
+// (attend_route.hpp).
 //
 // One workgroup owns one query tile: a base block of r queries (1D) or an
 // r x r cell (2D), 32 queries per wave.  It walks a list of 64-key tiles:
@@ -47,6 +47,7 @@
 // field's.
 #include "fma_device.hpp"
 #include "fma_kernels.hpp"
+#include "wave_ops.hpp"
 
 namespace fma_dev {
 
@@ -124,64 +125,18 @@ __device__ inline int swz_v(int row) { return 2 * (row & 3); }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// max of x over this lane and lane ^ 32
-__device__ inline float max_pair(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ inline float sum_pair(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ inline uint32_t pack_bf16(float lo, float hi)
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 p = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
-    return __builtin_bit_cast(uint32_t, p);
-}
-
 // A wave's O^T (rows channels, columns queries; scaled by inv) to bf16 rows of
 // 64 channels at base + token(row) * 64, in kStores store instructions.
-// Exchanges between lane halves and 16-lane rows first gather 64 consecutive
-// bytes of a row in four lanes, so that an instruction writes 16 half lines
-// instead of 8-byte pieces of 32 lines.
 constexpr int kStores = 4;
 template <typename F>
 __device__ __attribute__((always_inline)) inline void store_out(__bf16 *base, const f32x16 &o0, const f32x16 &o1,
                                                                 float inv, int lane, F token)
 {
-    const int l16 = lane & 15, chunk = 2 * ((lane >> 4) & 1) + (lane >> 5);
-    __bf16 *const r0 = base + token(l16) * kHeadDim + 8 * chunk;
-    __bf16 *const r1 = base + token(16 + l16) * kHeadDim + 8 * chunk;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const f32x16 &o = h ? o1 : o0;
-        uint32_t u[8];   // channels 32 h + 8 g + 4 (lane >> 5) + 2 k, + 1 of the lane's row in u[2 g + k]
-#pragma unroll
-        for (int x = 0; x < 8; ++x) u[x] = pack_bf16(o[2 * x] * inv, o[2 * x + 1] * inv);
-        // lane halves: whole 16-byte chunks, chunk 2 x + (lane >> 5) in u[4 x .. 4 x + 3]
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const auto r = __builtin_amdgcn_permlane32_swap(u[4 * x + k], u[4 * x + 2 + k], false, false);
-                u[4 * x + k] = r[0];
-                u[4 * x + 2 + k] = r[1];
-            }
-        // 16-lane rows: u[0 .. 3] for row l16, u[4 .. 7] for row 16 + l16
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const auto r = __builtin_amdgcn_permlane16_swap(u[k], u[4 + k], false, false);
-            u[k] = r[0];
-            u[4 + k] = r[1];
-        }
-        *reinterpret_cast<uint4 *>(r0 + 32 * h) = make_uint4(u[0], u[1], u[2], u[3]);
-        *reinterpret_cast<uint4 *>(r1 + 32 * h) = make_uint4(u[4], u[5], u[6], u[7]);
-    }
+    const int l16 = lane & 15;
+    __bf16 *const r0 = base + token(l16) * kHeadDim + 8 * store_chunk(lane);
+    __bf16 *const r1 = base + token(16 + l16) * kHeadDim + 8 * store_chunk(lane);
+    store_rows32(o0, inv, r0, r1);
+    store_rows32(o1, inv, r0 + 32, r1 + 32);
 }
 
 enum TileMask { MASK_NONE = 0, MASK_CAUSAL = 1, MASK_SLOTS = 2 };
@@ -245,7 +200,7 @@ __device__ __attribute__((always_inline)) inline void block_softmax_pv(
         for (int j = 0; j < 5; ++j)
             t[j] = fmaxf(fmaxf(3 * j >= lo ? sc[3 * j] : -INFINITY, 3 * j + 1 >= lo ? sc[3 * j + 1] : -INFINITY),
                          3 * j + 2 >= lo ? sc[3 * j + 2] : -INFINITY);
-        return max_pair(fmaxf(fmaxf(fmaxf(t[0], t[1]), t[2]), fmaxf(fmaxf(t[3], t[4]), sc[15])));
+        return pair_max(fmaxf(fmaxf(fmaxf(t[0], t[1]), t[2]), fmaxf(fmaxf(t[3], t[4]), sc[15])));
     };
     if constexpr (FIRST) {
         // the wave's first block, every key visible: m starts at its maximum
@@ -362,7 +317,7 @@ __device__ __attribute__((always_inline)) inline void block_levels_pv(
     if (grp >= 32) cm[0] = cm[1] = cm[2] = cm[3] = fmaxf(cm[0], cm[2]);
     if (grp >= 8) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) cm[c] = max_pair(cm[c]);
+        for (int c = 0; c < 4; ++c) cm[c] = pair_max(cm[c]);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -378,7 +333,7 @@ __device__ __attribute__((always_inline)) inline void block_levels_pv(
     if (grp >= 32) cl[0] = cl[1] = cl[2] = cl[3] = cl[0] + cl[2];
     if (grp >= 8) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) cl[c] = sum_pair(cl[c]);
+        for (int c = 0; c < 4; ++c) cl[c] = pair_sum(cl[c]);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -516,11 +471,8 @@ __device__ __attribute__((always_inline)) inline long long block_token(const QBl
 #ifndef FMA_NS_1D
 #define FMA_NS_1D 2       // LDS stages of those 1D kernels
 #endif
-// (2D pairs under the per-level normalisation keep the levels' own
-// accumulators as well: three waves per SIMD, whose register budget holds
-// them without spilling)
-template <int NW, int GEOM, bool PL = false>
-constexpr int kWavesPerEU = NW >= 4 ? (GEOM == GEOM_1D ? FMA_WAVES_1D : GEOM == GEOM_2DP ? (PL ? 3 : 4) : 3) : 2;
+template <int NW, int GEOM>
+constexpr int kWavesPerEU = NW >= 4 ? (GEOM == GEOM_1D ? FMA_WAVES_1D : 3) : 2;
 
 // LIN (FMA-linear): every query of a block scores its far field with the
 // same coarse queries (its block's own group at each level), so the far
@@ -530,14 +482,14 @@ constexpr int kWavesPerEU = NW >= 4 ? (GEOM == GEOM_1D ? FMA_WAVES_1D : GEOM == 
 // every block beforehand and every query folds them into its own (m, l, O)
 // before the output.
 template <int NW, int GEOM, bool PL, bool LIN>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NW, GEOM, PL>, kWavesPerEU<NW, GEOM, PL>)))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<NW, GEOM>, kWavesPerEU<NW, GEOM>)))
 void attend_mfma_kernel(AttnArgs a)
 {
     constexpr int NT = 64 * NW;
     // LDS stages: three (two tiles in flight) when four or more waves share
     // them, two for two-wave workgroups, whose LDS per wave is double.
     constexpr int NS = NW >= 4 ? (GEOM == GEOM_1D ? FMA_NS_1D : GEOM == GEOM_2DP ? 2 : FMA_NS_WIDE) : FMA_NS_NARROW;
-    static_assert(GEOM != GEOM_2DP || (NW == 4 && !LIN), "2D pairs: four waves, not FMA-linear");
+    static_assert(GEOM != GEOM_2DP || (NW == 4 && PL && !LIN), "2D pairs: four waves, levels wider than a block");
     constexpr int NLD = 16 / NW;   // fewest of a tile's 16 loads any wave issues
     constexpr int K = kIs2D<GEOM> ? kSlots2D : kSlots1D;
     // slot table: both cells' tables side by side in the paired kernel
@@ -1001,8 +953,8 @@ _Pragma("unroll")                                                               
         }
         // coarse tiles: gathered interaction-list rows, empty slots masked
         if constexpr (PL) {
-            const float lnear = sum_pair(lrun);   // the near field's row sum, final here
-            if (kIs2D<GEOM> && sgrp > 32) {
+            const float lnear = pair_sum(lrun);   // the near field's row sum, final here
+            if (GEOM == GEOM_2DP || (kIs2D<GEOM> && sgrp > 32)) {
                 // 2D rank p >= 2: a level's 27p slots fill sgrp / 32 whole
                 // blocks, so each level runs an online softmax of its own
                 // (max ml, this lane's half of the sum ll, accumulators
@@ -1042,7 +994,7 @@ _Pragma("unroll")                                                               
                                                  (uint32_t)(mlane >> (32 * sb)), !lseen, ol0, ol1, cl, ml, ll);
                         lseen = lseen || any;
                         if ((s0 + 32) % sgrp == 0 || s0 + 32 >= nslot) {
-                            const float lsum = sum_pair(ll);
+                            const float lsum = pair_sum(ll);
                             const float f = lsum > 0.f ? lnear / lsum : 0.f;
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
@@ -1053,16 +1005,10 @@ _Pragma("unroll")                                                               
                     }
                 }
             } else {
-                for (int ct = 0; ct < (GEOM == GEOM_2DP ? 2 : 1) * g.nctile; ++ct) {
+                for (int ct = 0; ct < g.nctile; ++ct) {
                     FMA_NEXT_TILE();
-                    int ctl = ct;
-                    if constexpr (GEOM == GEOM_2DP) {
-                        const int c_ = ct >= g.nctile ? 1 : 0;
-                        if (c_ != (wave >> 1)) continue;
-                        ctl = ct - c_ * g.nctile;
-                    }
                     const unsigned long long ml = sm.cmask[cst] >> (4 * hh);
-                    const int nsb = nslot - ctl * KT > 32 ? 2 : 1;
+                    const int nsb = nslot - ct * KT > 32 ? 2 : 1;
 #pragma unroll 1
                     for (int sb = 0; sb < nsb; ++sb)
                         block_levels_pv(block_scores(kt + sb * BLK, koff, qb, cneg), vt + sb * BLK, voff,
@@ -1070,18 +1016,10 @@ _Pragma("unroll")                                                               
                 }
             }
         } else {
-            // (2D pairs: the left cell's coarse tiles, then the right cell's,
-            // each taken by its own waves)
-            for (int ct = 0; ct < (GEOM == GEOM_2DP ? 2 : 1) * g.nctile; ++ct) {
+            for (int ct = 0; ct < g.nctile; ++ct) {
                 FMA_NEXT_TILE();
-                int ctl = ct;
-                if constexpr (GEOM == GEOM_2DP) {
-                    const int c_ = ct >= g.nctile ? 1 : 0;
-                    if (c_ != (wave >> 1)) continue;
-                    ctl = ct - c_ * g.nctile;
-                }
                 const unsigned long long ml = sm.cmask[cst] >> (4 * hh);
-                const int nsb = nslot - ctl * KT > 32 ? 2 : 1;
+                const int nsb = nslot - ct * KT > 32 ? 2 : 1;
 #pragma unroll 1
                 for (int sb = 0; sb < nsb; ++sb) {
                     attend_block<MASK_SLOTS>(kt + sb * BLK, vt + sb * BLK, koff, voff, qb, 0,
@@ -1108,7 +1046,7 @@ _Pragma("unroll")                                                               
         }
 
         // ---------------------------------------- block done: O = O^T / l
-        const float inv = 1.0f / sum_pair(lrun);
+        const float inv = 1.0f / pair_sum(lrun);
         store_out(outp + (long long)cb.slice * g.n * kHeadDim, o0, o1, inv, lane,
                   [&](int row) { return block_token<GEOM>(cb, g, wave * 32 + row); });
         stored = true;
@@ -1294,7 +1232,7 @@ hipError_t launch_attend_bf16(const AttnArgs &a, int geometry, hipStream_t st)
     if (a.norm_level && a.nslot > 0) {   // printed per-level normalisation
         if (geometry == GEOM_1D) return launch_geom<GEOM_1D, true>(a, st);
         if (geometry == GEOM_2D) {
-            if (pair_cells_2d(a.r, a.nby, a.nslot, a.norm_level, 0, 1)) return launch_nw<4, GEOM_2DP, true, false>(a, st);
+            if (pair_cells_2d(a.r, a.nby, a.nslot, a.slot_group)) return launch_nw<4, GEOM_2DP, true, false>(a, st);
             return launch_geom<GEOM_2D, true>(a, st);
         }
         return hipErrorInvalidValue;

@@ -48,7 +48,7 @@ inline unsigned attend_kernels(const AttnArgs &a, bool two_d)
     if (a.qbar) return a.nslot > 0 && !a.norm_level && a.rank == 1 ? ATTEND_STREAM : 0;   // FMA-linear
     if (!two_d) return a.r >= 128 ? ATTEND_STREAM : 0;
     if (!a.norm_level || a.nslot == 0) return 0;   // joint normalisation on maps: groups
-    return pair_cells_2d(a.r, a.nby, a.nslot, a.norm_level, 0, 1) ? ATTEND_PAIRS : ATTEND_STREAM;
+    return pair_cells_2d(a.r, a.nby, a.nslot, a.slot_group) ? ATTEND_PAIRS : ATTEND_STREAM;
 }
 
 // 1D blocks of 128 and 256 and bidirectional ones of 192 at d = 64, on a device

@@ -359,7 +359,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
             dpart += go.x[c] * ldf(op, qrow + 2 * c + hh, a.io_elems);
         }
     }
-    const float dq_row = psum(dpart);
+    const float dq_row = pair_sum(dpart);
     const float cs = a.scale_log2;
     const float off = cs < 0.f ? INFINITY : -INFINITY;   // a masked score: -inf once scaled
     // 1D: the last query of the workgroup; causal near tiles past it add nothing
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
             if (x + 1 < ntl1) kv.fetch(a, m, b, tile1(x + 1), slice, tid);
             if (!active) continue;
             if constexpr (PL)
-                if (x == nco1) dnear = dq_row - psum(dsum);   // the first near tile
+                if (x == nco1) dnear = dq_row - pair_sum(dsum);   // the first near tile
             const bool stats = wide && x < nco;   // wide levels: the stats sweep
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                             sc[i] = sm.valid[kr] != 0 ? sm.lins[kr] * cs : -INFINITY;
                             mxl = fmaxf(mxl, sc[i]);
                         }
-                        mxl = pmax(mxl);
+                        mxl = pair_max(mxl);
                         const bool raise = mxl > mrun + 8.0f;
                         if (__builtin_amdgcn_ballot_w64(raise) != 0) {
                             const float mnew = raise ? mxl : mrun;
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                             float bm = -INFINITY;
 #pragma unroll
                             for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[i]);
-                            const float mnew = fmaxf(gm, pmax(bm));
+                            const float mnew = fmaxf(gm, pair_max(bm));
                             const float mref = mnew > -INFINITY ? mnew : 0.f;
                             const float corr = gm > -INFINITY ? fexp2(gm - mref) : 0.f;
                             float bl = 0.f, bd = 0.f;
@@ -494,8 +494,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                                 bl += p;
                                 bd += p * dp[i];
                             }
-                            gl = gl * corr + psum(bl);
-                            gd = gd * corr + psum(bd);
+                            gl = gl * corr + pair_sum(bl);
+                            gd = gd * corr + pair_sum(bd);
                             gm = mnew;
                             if ((sb0 + 32) % grp == 0 || sb0 + 32 >= a.nslot) {
                                 const float dG = gl > 0.f ? gd / gl : 0.f;
@@ -597,7 +597,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                             s2[i] *= cs;
                             mx = fmaxf(mx, s2[i]);
                         }
-                        const float mnew = fmaxf(mrun, pmax(mx));
+                        const float mnew = fmaxf(mrun, pair_max(mx));
                         const float corr = fexp2(mrun - mnew);
                         lrun *= corr;
 #pragma unroll
@@ -626,7 +626,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                         s[i] *= cs;
                         mx = fmaxf(mx, s[i]);
                     }
-                    mx = pmax(mx);
+                    mx = pair_max(mx);
                     const bool raise = mx > mrun + 8.0f;
                     if (__builtin_amdgcn_ballot_w64(raise) != 0) {
                         const float mnew = raise ? mx : mrun;
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
             }
         }
     }
-    const float lsum = psum(lrun);
+    const float lsum = pair_sum(lrun);
     const float lse = mrun + __log2f(lsum);
     {
         const float f = lsum > 0.f ? a.scale / lsum : 0.f;
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                         float acc = 0.f;
 #pragma unroll
                         for (int i = 0; i < 16; ++i) acc += s2[i];
-                        cl = psum(acc);
+                        cl = pair_sum(acc);
                     }
                     sl_set = slot / K;
                     sl_set = sl_set < kMaxCoarse ? sl_set : kMaxCoarse - 1;
@@ -1573,8 +1573,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(BF16 &&
                 dkd += ko.x[c] * sm.cbar[0][2 * c + hh];
                 dvd += vo.x[c] * sm.cbar[1][2 * c + hh];
             }
-            dkd = psum(dkd);
-            dvd = psum(dvd);
+            dkd = pair_sum(dkd);
+            dvd = pair_sum(dvd);
             if (hh == 0 && klive) {
                 const long long di = ((long long)slice * a.lv.nlev + e) * a.n + ktok;
                 stf(a.dotk, di, a.dot_elems, dkd);

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
         for (int e = 0; e < 8; ++e) dpart += static_cast<float>(go.x[c][e]) * static_cast<float>(o[e]);
     }
-    const float dd = psum(dpart);
+    const float dd = pair_sum(dpart);
     __syncthreads();   // the set tables
     build_lists<GEOM>(a, m, gl, grp, sm.st, nct * KT, wave, lane, sm.list);
 
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             float mx = s[0] * cs;
 #pragma unroll
             for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i] * cs);
-            mrun = pmax(mx);
+            mrun = pair_max(mx);
             first = false;
         }
         // P against the reference maximum as it stands (it only keeps P
@@ -138,14 +138,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             bl += s[i];
         }
         if (__builtin_amdgcn_ballot_w64(bl > 0x1p64f) != 0) {
-            const bool raise = pmax(bl) > 0x1p64f;   // each query for itself
+            const bool raise = pair_max(bl) > 0x1p64f;   // each query for itself
             read_row(rop, kt, ro);
             s = contract_channels<true>(rop, qo, f32x16{0});
             mask_rows(s);
             float mx = -INFINITY;
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[i] * cs);
-            mx = pmax(mx);
+            mx = pair_max(mx);
             const float mnew = raise ? fmaxf(mrun, mx) : mrun;
             const float corr = fexp2(mrun - mnew);
             lrun *= corr;
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         }
     }
     if (!m.active) return;
-    const float lsum = psum(lrun);
+    const float lsum = pair_sum(lrun);
     if (hh == 0) {
         a.lse[(long long)slice * a.n + qtok] = mrun + __log2f(lsum);
         a.delta[(long long)slice * a.n + qtok] = dd;

@@ -5,6 +5,7 @@
 
 #include "fma_device.hpp"
 #include "fma_kernels.hpp"
+#include "wave_ops.hpp"
 
 namespace fma_dev {
 
@@ -213,19 +214,6 @@ __device__ inline f32x16 contract_rows_tr1(const __bf16 *tile, const bf16x8 pb[2
     return out;
 }
 
-// max / sum of x over this lane and lane ^ 32 (v_permlane32_swap: a VALU
-// exchange of the wave's halves, no LDS round trip)
-__device__ inline float pmax(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ inline float psum(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // Per-level softmax of one 32-slot block of scores (per-level
 // normalisation): the slots form aligned groups of grp (4, 8, 16 or 32)
 // rows, one level each.  x holds the lane's scaled scores (log2 units, -inf
@@ -247,7 +235,7 @@ __device__ inline void level_block(f32x16 &x, const f32x16 &dp, int grp, float (
     if (grp >= 32) cm[0] = cm[1] = cm[2] = cm[3] = fmaxf(cm[0], cm[2]);
     if (grp >= 8) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) cm[c] = pmax(cm[c]);
+        for (int c = 0; c < 4; ++c) cm[c] = pair_max(cm[c]);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -263,7 +251,7 @@ __device__ inline void level_block(f32x16 &x, const f32x16 &dp, int grp, float (
     if (grp >= 32) cl[0] = cl[1] = cl[2] = cl[3] = cl[0] + cl[2];
     if (grp >= 8) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) cl[c] = psum(cl[c]);
+        for (int c = 0; c < 4; ++c) cl[c] = pair_sum(cl[c]);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -280,7 +268,7 @@ __device__ inline void level_block(f32x16 &x, const f32x16 &dp, int grp, float (
     if (grp >= 32) cd[0] = cd[1] = cd[2] = cd[3] = cd[0] + cd[2];
     if (grp >= 8) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) cd[c] = psum(cd[c]);
+        for (int c = 0; c < 4; ++c) cd[c] = pair_sum(cd[c]);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {

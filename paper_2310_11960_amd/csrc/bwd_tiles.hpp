@@ -93,55 +93,15 @@ __device__ inline void read_row(RowOp<true> &op, const __bf16 *tile, const RowOf
 }
 
 // A wave's 32 x 64 result (accumulators: rows channels, columns rows of the
-// result) to bf16 rows of 64 channels at base + token(row) * 64.  Exchanges
-// between lane halves and 16-lane rows first gather 64 consecutive bytes of a
-// row in four lanes, so that a store instruction writes 16 half lines instead
-// of 8-byte pieces of 32 lines.
+// result) to bf16 rows of 64 channels at base + token(row) * 64.
 template <typename F>
 __device__ inline void store_rows(__bf16 *base, const f32x16 &o0, const f32x16 &o1, int lane, F token)
 {
-    // u[h][2 g + k]: channels 32 h + 8 g + 4 hh + 2 k, + 1 of row l32
-    uint32_t u[2][8];
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-            const bf16x2 p = {static_cast<__bf16>(o0[4 * g + 2 * k]), static_cast<__bf16>(o0[4 * g + 2 * k + 1])};
-            const bf16x2 q = {static_cast<__bf16>(o1[4 * g + 2 * k]), static_cast<__bf16>(o1[4 * g + 2 * k + 1])};
-            u[0][2 * g + k] = __builtin_bit_cast(uint32_t, p);
-            u[1][2 * g + k] = __builtin_bit_cast(uint32_t, q);
-        }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        // lane halves: afterwards a lane holds whole 16-byte chunks, chunk
-        // 2 x + hh of its row in u[4 x .. 4 x + 3], x = 0, 1
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const auto r = __builtin_amdgcn_permlane32_swap(u[h][4 * x + k], u[h][4 * x + 2 + k], false, false);
-                u[h][4 * x + k] = r[0];
-                u[h][4 * x + 2 + k] = r[1];
-            }
-        // 16-lane rows: lanes of rows l and l + 16 trade chunk pairs, so that
-        // u[0 .. 3] belongs to row l32 & 15 and u[4 .. 7] to row 16 + (l32 & 15),
-        // chunk 2 (l32 >> 4) + hh of both
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const auto r = __builtin_amdgcn_permlane16_swap(u[h][k], u[h][4 + k], false, false);
-            u[h][k] = r[0];
-            u[h][4 + k] = r[1];
-        }
-    }
-    const int l16 = lane & 15, chunk = 2 * ((lane >> 4) & 1) + (lane >> 5);
-    __bf16 *const r0 = base + (long long)token(l16) * kHeadDim + 8 * chunk;
-    __bf16 *const r1 = base + (long long)token(16 + l16) * kHeadDim + 8 * chunk;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        *reinterpret_cast<uint4 *>(r0 + 32 * h) = make_uint4(u[h][0], u[h][1], u[h][2], u[h][3]);
-        *reinterpret_cast<uint4 *>(r1 + 32 * h) = make_uint4(u[h][4], u[h][5], u[h][6], u[h][7]);
-    }
+    const int l16 = lane & 15;
+    __bf16 *const r0 = base + (long long)token(l16) * kHeadDim + 8 * store_chunk(lane);
+    __bf16 *const r1 = base + (long long)token(16 + l16) * kHeadDim + 8 * store_chunk(lane);
+    store_rows32(o0, 1.f, r0, r1);
+    store_rows32(o1, 1.f, r0 + 32, r1 + 32);
 }
 
 // A wave's 32 x 64 result to fp32 rows of 64 channels, row l32 at `row` (of

@@ -1122,8 +1122,8 @@ extern "C" fma_status_t fma_plan_params(fma_plan_t p, int64_t *out, int32_t capa
         (int64_t)p->part_offset, (int64_t)p->coarse_bytes, (int64_t)p->ws_bytes, p->linear,
         p->desc.weights_per_head ? heads : 1, p->desc.dtype};
     for (int i = 0; i < 36; ++i) out[i] = v[i];
-    out[36] = p->desc.ndim == 2 && !p->generic &&
-              fma_dev::pair_cells_2d(p->r, p->nby, p->nslot, p->norm_level, p->linear, p->desc.dtype == FMA_BF16);
+    out[36] = p->desc.ndim == 2 && !p->generic && p->norm_level && p->desc.dtype == FMA_BF16 &&
+              fma_dev::pair_cells_2d(p->r, p->nby, p->nslot, p->slot_group);
     out[37] = p->H;
     out[38] = p->nby;
     out[39] = p->tiles_x;

@@ -123,20 +123,19 @@ __host__ __device__ inline int list2d_entry(int cx, int cy, int l, int j, int Mx
     return u * My + v;
 }
 
-// Whether the bf16 fused attention walks a 2D map two horizontally adjacent
-// cells per workgroup (cells (x, 2c) and (x, 2c + 1), four waves): their
-// near fields share six of their nine cells, so the pair loads 12 near tiles
-// where two single cells load 18, and twice the waves share the LDS stages.
-// Used for 8 x 8 cells on maps with an even number of cell columns (nby),
-// either normalisation, without query downsampling, and when both cells'
-// interaction-list tables fit the paired kernel's slot table
+// Whether the bf16 stream walks a per-level 2D map two horizontally adjacent
+// cells per workgroup (cells (x, 2c) and (x, 2c + 1), four waves): their near
+// fields share six of their nine cells, so the pair loads 12 near tiles where
+// two single cells load 18, and twice the waves share the LDS stages.  For
+// levels of several 32-slot blocks (rank 2 and more; the rest run on
+// attend_group.hip) on 8 x 8 cells, maps with an even number of cell columns
+// (nby), and lists that fit the paired kernel's slot table twice
 // (kMaxPairSlotTable; the other kernels' table holds kMaxSlotTable slots).
 constexpr int kMaxSlotTable = 448;
 constexpr int kMaxPairSlotTable = 768;
-__host__ __device__ constexpr bool pair_cells_2d(int r, int nby, int nslot, [[maybe_unused]] int norm_level, int linear,
-                                                 int bf16)
+__host__ __device__ constexpr bool pair_cells_2d(int r, int nby, int nslot, int slot_group)
 {
-    return bf16 && !linear && r == 8 && nby % 2 == 0 && nslot <= kMaxSlotTable &&
+    return r == 8 && nby % 2 == 0 && slot_group > 32 && nslot > 0 && nslot <= kMaxSlotTable &&
            2 * ((nslot + 63) / 64) * 64 <= kMaxPairSlotTable;
 }
 

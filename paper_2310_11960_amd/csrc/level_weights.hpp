@@ -1,24 +1,12 @@
 // level_weights.hpp -- the printed per-level normalisation of one 32-key block
-// of coarse scores, and exchanges between the halves of a wave.
+// of coarse scores.
 #pragma once
 
-#include "fma_device.hpp"
+#include "wave_ops.hpp"
 
 namespace fma_dev {
 
 namespace {
-
-// max / sum of x over this lane and lane ^ 32 (v_permlane32_swap)
-__device__ __attribute__((always_inline)) inline float pair_max(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __attribute__((always_inline)) inline float pair_sum(float x)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 // Printed per-level normalisation of one 32-key block of coarse scores x
 // (log2 units, masked slots -inf): the keys form aligned groups of grp (4, 8,
