@@ -92,16 +92,8 @@ void attend_group_kernel(AttnArgs a)
     // Tile t into stage st: NLD loads per tensor, wave w takes w, w + 4, .. of both
     auto issue = [&](int t, int st) __attribute__((always_inline)) {
         const bool co = t >= nnear;
-        long long base = 0;   // 2D: first token of the tile's cell
-        int p0 = 0;
-        if constexpr (GEOM != GEOM_1D) {
-            constexpr int lg = GEOM == GEOM_2DP ? 3 : 4;
-            if (!co) {
-                const int c = (t * TR) >> (2 * lg), cc = c / m.ncx, row = c - cc * m.ncx, col = window_col<GEOM>(a, m, cc);
-                p0 = (t * TR) & ((1 << 2 * lg) - 1);
-                base = (long long)((m.x0 + row) << lg) * a.side + (col << lg);
-            }
-        }
+        TileCell cell = {0, 0};
+        if (!co) cell = tile_cell<GEOM, TR>(a, m, t);
 #pragma unroll
         for (int jj = 0; jj < NLD / 4; ++jj) {
             const int i = wave + 4 * jj, row = i * RI + lr;
@@ -113,15 +105,7 @@ void attend_group_kernel(AttnArgs a)
                 dma16(kb + r, kd);
                 dma16(vb + r, vd);
             } else {
-                long long r;
-                if constexpr (GEOM == GEOM_1D) {
-                    r = m.lo + (long long)t * TR + row;
-                    r = r < a.n ? r : a.n - 1;
-                } else {
-                    constexpr int lg = GEOM == GEOM_2DP ? 3 : 4;
-                    const int p = p0 + row;
-                    r = base + (long long)(p >> lg) * a.side + (p & ((1 << lg) - 1));
-                }
+                const long long r = tile_token<GEOM, TR>(a, m, cell, t, row);
                 dma16(kg + r * RB + ch, kd);
                 dma16(vg + r * RB + ch, vd);
             }
@@ -138,7 +122,7 @@ void attend_group_kernel(AttnArgs a)
         for (int c = 0; c < NC; ++c) qo[c] = *reinterpret_cast<const bf16x8 *>(qp + 16 * c);
     }
     __syncthreads();   // the set tables
-    build_lists<GEOM, PL>(a, m, gl, grp, sm.st, (gl.npiece + 1) / 2 * 64, wave, lane, sm.list);
+    build_lists<GEOM, PL>(a, m, gl, grp, sm.st, wave, lane, sm.list);
 
     // operand offsets (elements) in a tile: chunk 2 c + hh of row l32 is
     // koff ^ 16 c; the transposing reads of channels 32 db .. and rows 0 .. 15

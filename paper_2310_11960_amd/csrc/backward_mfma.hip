@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     const float dd = pair_sum(dpart);
     __syncthreads();   // the set tables
-    build_lists<GEOM>(a, m, gl, grp, sm.st, nct * KT, wave, lane, sm.list);
+    build_lists<GEOM>(a, m, gl, grp, sm.st, wave, lane, sm.list);
 
     const float cs = a.scale_log2;
     const float off = cs < 0.f ? INFINITY : -INFINITY;   // a masked score: -inf once scaled
@@ -230,7 +230,6 @@ struct CoarseSmem {
 template <bool TWO_D>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 3))) void bwd_coarse_mfma(BwdArgs a)
 {
-    constexpr int K = TWO_D ? kSlots2D : kSlots1D;
     __shared__ __attribute__((aligned(16))) CoarseSmem sm;
     const int lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
     const int npc = (a.gslot + 31) / 32;
@@ -240,53 +239,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 3))) void
     const int ls = (int)(gid / (unsigned)a.ngrp), grp = (int)(gid - (unsigned)ls * (unsigned)a.ngrp);
     const int slice = a.slice0 + ls;
 
-    // the group's blocks: 1D blocks 2 grp, 2 grp + 1; 2D cells (cx0 + i, cy0 + j)
-    int cx0 = 2 * grp, cy0 = 0, ncx, ncy = 1, cpb;   // blocks per axis, chunks per block
-    if constexpr (TWO_D) {
-        const int ngy = (a.nby + 1) >> 1;
-        cx0 = 2 * (grp / ngy);
-        cy0 = 2 * (grp - (grp / ngy) * ngy);
-        ncy = a.nby - cy0 < 2 ? 1 : 2;
-        cpb = a.r * a.r / 32;
-    } else {
-        cpb = a.r / 32;
-    }
-    ncx = a.nbx - cx0 < 2 ? 1 : 2;
-    const int nchunk = ncx * ncy * cpb;
+    const SiblingGroup sg = sibling_group<TWO_D>(a, grp);
+    const int nchunk = sg.ncx * sg.ncy * sg.cpb;
 
-    // this lane's slot: its coarse row and the blocks (bit 2 i + j) that list it
-    const int slot = pc * 32 + l32;
-    int row = 0, mask = 0;
-    if (slot < a.gslot) {
-        const int nw = a.rank * group_window(TWO_D);
-        if (slot < nw) {
-            const int set = slot / group_window(TWO_D), pos = slot - set * group_window(TWO_D);
-            const int u = cx0 - 2 + (TWO_D ? pos / 6 : pos), v = TWO_D ? cy0 - 2 + pos % 6 : 0;
-            if (u >= 0 && u < a.lv.M[set] && (!TWO_D || (v >= 0 && v < a.lv.My[set]))) {
-                row = a.lv.off[set] + (TWO_D ? u * a.lv.My[set] + v : u);
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < (TWO_D ? 2 : 1); ++j) {
-                        const int du = u - cx0 - i, dv = v - cy0 - j;
-                        bool near = du >= -1 && du <= 1 && (!TWO_D || (dv >= -1 && dv <= 1));
-                        if (!TWO_D && a.causal) near = du > -2;
-                        mask |= near ? 0 : 1 << (2 * i + j);
-                    }
-            }
-        } else {
-            const int set = a.rank + (slot - nw) / K, j = (slot - nw) % K;
-            int g;
-            if constexpr (TWO_D)
-                g = list2d_entry(cx0, cy0, a.lv.lvl[set], j, a.lv.M[set], a.lv.My[set]);
-            else
-                g = list1d_entry(cx0, a.lv.lvl[set], j, a.lv.M[set], a.causal);
-            if (g >= 0) {
-                row = a.lv.off[set] + g;
-                mask = 15;
-            }
-        }
-    }
+    // this lane's slot: its coarse row and the blocks that list it
+    int mask;
+    const int row = sibling_slot<TWO_D>(a, sg, a.gslot, pc * 32 + l32, mask);
     RowOp<true> ko, vn;   // the slot's rows (V negated, as in the key pass)
     const long long crow = ((long long)slice * a.R + row) * kHeadDim;
 #pragma unroll
@@ -305,22 +263,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 3))) void
     const float *const lg = a.lse + (long long)slice * a.n;
     const float *const dg = a.delta + (long long)slice * a.n;
     const int loff0 = dma_lane_off(lane, 0), loff1 = dma_lane_off(lane, 1);
-    const int lgr = 31 - __builtin_clz(a.r);
-    auto block_of = [&](int c, int &i, int &j, int &p) {   // block (i, j) of chunk c and the chunk's position in it
-        const int b = c / cpb;
-        i = b / ncy;
-        j = b - i * ncy;
-        p = 32 * (c - b * cpb);
-    };
-    auto run_tok = [&](int c, int i8) {   // first token of rows 8 i8 .. of chunk c
-        int i, j, p;
-        block_of(c, i, j, p);
-        p += 8 * i8;
-        if constexpr (TWO_D)
-            return (long long)(((cx0 + i) << lgr) + (p >> lgr)) * a.side + ((cy0 + j) << lgr) + (p & (a.r - 1));
-        else
-            return (long long)(cx0 + i) * a.r + p;
-    };
+    auto run_tok = [&](int c, int i8) { return sibling_run<TWO_D>(a, sg, c, i8); };
     auto issue = [&](int c, int st) {   // nine loads
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -346,7 +289,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 3))) void
             wait_vm<0>();
         }
         int bi, bj, bp;
-        block_of(c, bi, bj, bp);
+        sibling_block(sg, c, bi, bj, bp);
         const bool on = (mask >> (2 * bi + bj)) & 1;
         RowOp<true> rop;
         read_row(rop, sm.q[st], ro);

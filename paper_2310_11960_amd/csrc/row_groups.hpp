@@ -51,7 +51,7 @@ __device__ __attribute__((always_inline)) inline uint32_t lds_u32(const void *p)
 // Position of workgroup `bid` of `total` when the eight XCDs, which take
 // workgroups round-robin, each walk one contiguous range: neighbouring groups,
 // which share most of their near window, meet in one XCD's L2.
-__device__ __attribute__((always_inline)) inline unsigned xcd_contiguous(unsigned bid, unsigned total)
+__host__ __device__ __attribute__((always_inline)) inline unsigned xcd_contiguous(unsigned bid, unsigned total)
 {
     const unsigned x = bid & 7, j = bid >> 3, per = total >> 3, rem = total & 7;
     return x * per + (x < rem ? x : rem) + j;
@@ -82,7 +82,7 @@ __host__ __device__ inline long long row_groups(const A &a)
 // queries that may see them (causal: those at or after the key); else rows
 // are queries and the window holds their near keys.
 template <int GEOM, bool KEYS, typename A>
-__device__ __attribute__((always_inline)) inline RowGroup row_group(const A &a, int g, int wave)
+__host__ __device__ __attribute__((always_inline)) inline RowGroup row_group(const A &a, int g, int wave)
 {
     RowGroup m;
     m.lo = 0;
@@ -148,7 +148,7 @@ __device__ __attribute__((always_inline)) inline RowGroup row_group(const A &a, 
 // columns that both cells see first, then the left cell's, then the right
 // cell's, so that both cells start from the same cell; else ascending.
 template <int GEOM, typename A>
-__device__ __attribute__((always_inline)) inline int window_col(const A &a, const RowGroup &m, int cc)
+__host__ __device__ __attribute__((always_inline)) inline int window_col(const A &a, const RowGroup &m, int cc)
 {
     if constexpr (GEOM == GEOM_2DP) {
         if (a.nby % 2 == 0) {
@@ -163,7 +163,7 @@ __device__ __attribute__((always_inline)) inline int window_col(const A &a, cons
 // cells); rows past the window stay in the sequence (1D: repeat its end) or map
 // (2D: the caller stops at whole cells).
 template <int GEOM, typename A>
-__device__ __attribute__((always_inline)) inline long long window_run(const A &a, const RowGroup &m, int x)
+__host__ __device__ __attribute__((always_inline)) inline long long window_run(const A &a, const RowGroup &m, int x)
 {
     if constexpr (GEOM == GEOM_1D) {
         const long long tok = m.lo + 8 * (long long)x;
@@ -178,9 +178,41 @@ __device__ __attribute__((always_inline)) inline long long window_run(const A &a
     }
 }
 
+// Row `row` of tile t (TR rows) of the attention's near window: 1D consecutive
+// tokens, the last of the sequence repeated past its end; 2D pixel p0 + row of
+// the tile's cell (whole cells, so that no tile leaves the window).
+struct TileCell {
+    long long base;   // 2D: first token of the cell
+    int p0;
+};
+template <int GEOM, int TR, typename A>
+__host__ __device__ __attribute__((always_inline)) inline TileCell tile_cell(const A &a, const RowGroup &m, int t)
+{
+    TileCell r = {0, 0};
+    if constexpr (GEOM != GEOM_1D) {
+        constexpr int lg = GEOM == GEOM_2DP ? 3 : 4;
+        const int c = (t * TR) >> (2 * lg), cc = c / m.ncx, row = c - cc * m.ncx, col = window_col<GEOM>(a, m, cc);
+        r.p0 = (t * TR) & ((1 << 2 * lg) - 1);
+        r.base = (long long)((m.x0 + row) << lg) * a.side + (col << lg);
+    }
+    return r;
+}
+template <int GEOM, int TR, typename A>
+__host__ __device__ __attribute__((always_inline)) inline long long tile_token(const A &a, const RowGroup &m, const TileCell &c, int t, int row)
+{
+    if constexpr (GEOM == GEOM_1D) {
+        const long long tok = m.lo + (long long)t * TR + row;
+        return tok < a.n ? tok : a.n - 1;
+    } else {
+        constexpr int lg = GEOM == GEOM_2DP ? 3 : 4;
+        const int p = c.p0 + row;
+        return c.base + (long long)(p >> lg) * a.side + (p & ((1 << lg) - 1));
+    }
+}
+
 // Whether this wave takes piece p (rows 32 p .. 32 p + 31) of the window.
 template <int GEOM, typename A>
-__device__ __attribute__((always_inline)) inline bool piece_used(const A &a, const RowGroup &m, int p)
+__host__ __device__ __attribute__((always_inline)) inline bool piece_used(const A &a, const RowGroup &m, int p)
 {
     if (!m.active) return false;
     if constexpr (GEOM == GEOM_1D) {
@@ -195,7 +227,7 @@ __device__ __attribute__((always_inline)) inline bool piece_used(const A &a, con
 
 // Token of position p of the wave's base block
 template <int GEOM, typename A>
-__device__ __attribute__((always_inline)) inline long long wave_token(const A &a, const RowGroup &m, int p)
+__host__ __device__ __attribute__((always_inline)) inline long long wave_token(const A &a, const RowGroup &m, int p)
 {
     if constexpr (GEOM == GEOM_1D) {
         return (long long)m.blk * a.r + p;
@@ -230,7 +262,7 @@ __device__ __attribute__((always_inline)) inline void load_sets(SetTab &t, const
 // level-1 window, shared lists), seen by each cell through a bit mask; 16 x 16
 // cells their own list.  PL (per-level normalisation, levels padded to
 // slot_group slots): every block's or cell's own list, also for pairs.
-constexpr int kGroupRows = 768;   // most list rows: 1D <= 4 blocks x 192, 2D <= 576
+constexpr int kGroupRows = 768;   // most list rows (group_lists_fit): 1D 4 blocks of 32 x 192, 2D joint 576, PL pairs 2 x 384
 
 struct GroupLists {
     int nslot;            // slots per list
@@ -250,7 +282,7 @@ struct ListSmem {
 };
 
 template <int GEOM, bool PL = false, typename A>
-__device__ __attribute__((always_inline)) inline GroupLists group_lists(const A &a, const RowGroup &m, int grp, int wave = 0)
+__host__ __device__ __attribute__((always_inline)) inline GroupLists group_lists(const A &a, const RowGroup &m, int grp, int wave = 0)
 {
     GroupLists l;
     l.b0 = GEOM == GEOM_1D ? 128 * grp / a.r : 0;
@@ -263,66 +295,81 @@ __device__ __attribute__((always_inline)) inline GroupLists group_lists(const A 
     return l;
 }
 
-// Fill the group's list table, `rows` (a multiple of 64) of them, by four waves.
-template <int GEOM, bool PL = false, typename A>
-__device__ __attribute__((always_inline)) inline void build_lists(const A &a, const RowGroup &m, const GroupLists &l, int grp, const SetTab &st,
-                                   int rows, int wave, int lane, ListSmem &ls)
+// Coarse row of list row e of a group (-1: empty), and which of a 2D pair's
+// cells see it (else bit 0).
+template <int GEOM, bool PL = false, typename A, typename T>
+__host__ __device__ __attribute__((always_inline)) inline int list_row(const A &a, const RowGroup &m, const GroupLists &l, int grp, const T &st, int e, int &mask)
 {
     constexpr int K = GEOM == GEOM_1D ? kSlots1D : kSlots2D;
-    for (int e0 = 64 * wave; e0 < rows; e0 += 256) {
-        const int e = e0 + lane;
-        int row = -1, mask = 0;
-        if constexpr (GEOM == GEOM_1D || PL) {
-            const int bl = e / (32 * l.npc), sl = e - bl * 32 * l.npc;
-            int set = sl / K, j = sl - set * K;
-            bool on = bl < l.nb && sl < l.nslot;
-            if constexpr (PL) {
-                const int lev = sl / a.slot_group, rem = sl - lev * a.slot_group, basis = rem / K;
-                set = lev * a.rank + basis;
-                j = rem - basis * K;
-                on = on && basis < a.rank;
+    int row = -1;
+    mask = 0;
+    if constexpr (GEOM == GEOM_1D || PL) {
+        const int bl = e / (32 * l.npc), sl = e - bl * 32 * l.npc;
+        int set = sl / K, j = sl - set * K;
+        bool on = bl < l.nb && sl < l.nslot;
+        if constexpr (PL) {
+            const int lev = sl / a.slot_group, rem = sl - lev * a.slot_group, basis = rem / K;
+            set = lev * a.rank + basis;
+            j = rem - basis * K;
+            on = on && basis < a.rank;
+        }
+        if (on) {
+            int g;
+            if constexpr (GEOM == GEOM_1D) {
+                g = list1d_entry(l.b0 + bl, st.lvl[set], j, st.M[set], a.causal);
+            } else {
+                const int npr = (a.nby + 1) >> 1;
+                const int cx = GEOM == GEOM_2DP ? grp / npr : m.blk / a.nby;
+                const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * npr) + bl : m.blk - (m.blk / a.nby) * a.nby;
+                g = list2d_entry(cx, cy, st.lvl[set], j, st.M[set], st.My[set]);
             }
-            if (on) {
-                int g;
-                if constexpr (GEOM == GEOM_1D) {
-                    g = list1d_entry(l.b0 + bl, st.lvl[set], j, st.M[set], a.causal);
-                } else {
-                    const int npr = (a.nby + 1) >> 1;
-                    const int cx = GEOM == GEOM_2DP ? grp / npr : m.blk / a.nby;
-                    const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * npr) + bl : m.blk - (m.blk / a.nby) * a.nby;
-                    g = list2d_entry(cx, cy, st.lvl[set], j, st.M[set], st.My[set]);
+            if (g >= 0) {
+                row = st.off[set] + g;
+                mask = 1;
+            }
+        }
+    } else {
+        const int cx = GEOM == GEOM_2DP ? grp / ((a.nby + 1) >> 1) : m.blk / a.nby;
+        const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * ((a.nby + 1) >> 1)) : m.blk - (m.blk / a.nby) * a.nby;
+        if (e < l.nslot) {
+            const int nw = GEOM == GEOM_2DP ? a.rank * group_window(1) : 0;
+            if (e < nw) {
+                const int set = e / 36, pos = e - set * 36;
+                const int u = 2 * (cx >> 1) - 2 + pos / 6, v = 2 * (cy >> 1) - 2 + pos % 6;
+                if (u >= 0 && u < st.M[set] && v >= 0 && v < st.My[set]) {
+                    row = st.off[set] + u * st.My[set] + v;
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const int du = u - cx, dv = v - cy - c;
+                        mask |= (du < -1 || du > 1 || dv < -1 || dv > 1) ? 1 << c : 0;
+                    }
                 }
+            } else {
+                const int set = (GEOM == GEOM_2DP ? a.rank : 0) + (e - nw) / K, j = (e - nw) % K;
+                const int g = list2d_entry(cx, cy, st.lvl[set], j, st.M[set], st.My[set]);
                 if (g >= 0) {
                     row = st.off[set] + g;
-                    mask = 1;
-                }
-            }
-        } else {
-            const int cx = GEOM == GEOM_2DP ? grp / ((a.nby + 1) >> 1) : m.blk / a.nby;
-            const int cy = GEOM == GEOM_2DP ? 2 * (grp - cx * ((a.nby + 1) >> 1)) : m.blk - (m.blk / a.nby) * a.nby;
-            if (e < l.nslot) {
-                const int nw = GEOM == GEOM_2DP ? a.rank * group_window(1) : 0;
-                if (e < nw) {
-                    const int set = e / 36, pos = e - set * 36;
-                    const int u = 2 * (cx >> 1) - 2 + pos / 6, v = 2 * (cy >> 1) - 2 + pos % 6;
-                    if (u >= 0 && u < st.M[set] && v >= 0 && v < st.My[set]) {
-                        row = st.off[set] + u * st.My[set] + v;
-#pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            const int du = u - cx, dv = v - cy - c;
-                            mask |= (du < -1 || du > 1 || dv < -1 || dv > 1) ? 1 << c : 0;
-                        }
-                    }
-                } else {
-                    const int set = (GEOM == GEOM_2DP ? a.rank : 0) + (e - nw) / K, j = (e - nw) % K;
-                    const int g = list2d_entry(cx, cy, st.lvl[set], j, st.M[set], st.My[set]);
-                    if (g >= 0) {
-                        row = st.off[set] + g;
-                        mask = 3;
-                    }
+                    mask = 3;
                 }
             }
         }
+    }
+    return row;
+}
+
+// Rows of a group's list table: its pieces, in pairs.
+__host__ __device__ __attribute__((always_inline)) inline int list_table_rows(const GroupLists &l) { return (l.npiece + 1) / 2 * 64; }
+
+// Fill the group's list table by four waves.
+template <int GEOM, bool PL = false, typename A>
+__device__ __attribute__((always_inline)) inline void build_lists(const A &a, const RowGroup &m, const GroupLists &l, int grp,
+                                                                  const SetTab &st, int wave, int lane, ListSmem &ls)
+{
+    const int rows = list_table_rows(l);
+    for (int e0 = 64 * wave; e0 < rows; e0 += 256) {
+        const int e = e0 + lane;
+        int mask;
+        const int row = list_row<GEOM, PL>(a, m, l, grp, st, e, mask);
         const uint32_t on32 = (uint32_t)(__builtin_amdgcn_ballot_w64(row >= 0) >> (lane & 32));
         const int sub = __shfl(row, (lane & 32) + (on32 ? __builtin_ctz(on32) : 0));
         ls.crow[e] = row < 0 ? sub : row;
@@ -335,6 +382,89 @@ __device__ __attribute__((always_inline)) inline void build_lists(const A &a, co
             }
         }
     }
+}
+
+// A sibling group of base blocks (group_slots): 1D blocks 2 grp, 2 grp + 1; 2D
+// the 2 x 2 cells of a parent square, fewer at the end of the map.
+struct SiblingGroup {
+    int cx0, cy0;   // its first block / cell
+    int ncx, ncy;   // blocks per axis
+    int cpb;        // 32-row chunks per block
+    int lgr;        // log2 of the cell side
+};
+template <bool TWO_D, typename A>
+__host__ __device__ __attribute__((always_inline)) inline SiblingGroup sibling_group(const A &a, int grp)
+{
+    SiblingGroup s;
+    s.cx0 = 2 * grp;
+    s.cy0 = 0;
+    s.ncy = 1;
+    s.lgr = 31 - __builtin_clz(a.r);
+    if constexpr (TWO_D) {
+        const int ngy = (a.nby + 1) >> 1;
+        s.cx0 = 2 * (grp / ngy);
+        s.cy0 = 2 * (grp - (grp / ngy) * ngy);
+        s.ncy = a.nby - s.cy0 < 2 ? 1 : 2;
+        s.cpb = a.r * a.r / 32;
+    } else {
+        s.cpb = a.r / 32;
+    }
+    s.ncx = a.nbx - s.cx0 < 2 ? 1 : 2;
+    return s;
+}
+// Block (i, j) of the group's chunk c and the chunk's position p in it
+__host__ __device__ __attribute__((always_inline)) inline void sibling_block(const SiblingGroup &s, int c, int &i, int &j, int &p)
+{
+    const int b = c / s.cpb;
+    i = b / s.ncy;
+    j = b - i * s.ncy;
+    p = 32 * (c - b * s.cpb);
+}
+// First of the eight consecutive tokens of rows 8 i8 .. of chunk c
+template <bool TWO_D, typename A>
+__host__ __device__ __attribute__((always_inline)) inline long long sibling_run(const A &a, const SiblingGroup &s, int c, int i8)
+{
+    int i, j, p;
+    sibling_block(s, c, i, j, p);
+    p += 8 * i8;
+    if constexpr (TWO_D)
+        return (long long)(((s.cx0 + i) << s.lgr) + (p >> s.lgr)) * a.side + ((s.cy0 + j) << s.lgr) + (p & (a.r - 1));
+    else
+        return (long long)(s.cx0 + i) * a.r + p;
+}
+// Coarse row of a slot of the group (0 where it has none) and the blocks (bit
+// 2 i + j) that list it
+template <bool TWO_D, typename A>
+__host__ __device__ __attribute__((always_inline)) inline int sibling_slot(const A &a, const SiblingGroup &s, int gslot, int slot, int &mask)
+{
+    constexpr int K = TWO_D ? kSlots2D : kSlots1D;
+    mask = 0;
+    if (slot >= gslot) return 0;
+    const int nw = a.rank * group_window(TWO_D);
+    if (slot < nw) {
+        const int set = slot / group_window(TWO_D), pos = slot - set * group_window(TWO_D);
+        const int u = s.cx0 - 2 + (TWO_D ? pos / 6 : pos), v = TWO_D ? s.cy0 - 2 + pos % 6 : 0;
+        if (u < 0 || u >= a.lv.M[set] || (TWO_D && (v < 0 || v >= a.lv.My[set]))) return 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < (TWO_D ? 2 : 1); ++j) {
+                const int du = u - s.cx0 - i, dv = v - s.cy0 - j;
+                bool near = du >= -1 && du <= 1 && (!TWO_D || (dv >= -1 && dv <= 1));
+                if (!TWO_D && a.causal) near = du > -2;
+                mask |= near ? 0 : 1 << (2 * i + j);
+            }
+        return a.lv.off[set] + (TWO_D ? u * a.lv.My[set] + v : u);
+    }
+    const int set = a.rank + (slot - nw) / K, j = (slot - nw) % K;
+    int g;
+    if constexpr (TWO_D)
+        g = list2d_entry(s.cx0, s.cy0, a.lv.lvl[set], j, a.lv.M[set], a.lv.My[set]);
+    else
+        g = list1d_entry(s.cx0, a.lv.lvl[set], j, a.lv.M[set], a.causal);
+    if (g < 0) return 0;
+    mask = 15;
+    return a.lv.off[set] + g;
 }
 
 // Whether a group's list table fits (host).

@@ -6,7 +6,7 @@ restates, statement by statement, how the kernels form every global address,
 LDS destination, ring slot and staged output row, and checks them against the
 buffers' sizes and against what the data layout says they must be:
 
-  attend_mfma_kernel / attend_kernel tile stream (attend_mfma.hip):
+  attend_mfma_kernel tile stream (attend_mfma.hip), for the plans that take it:
     - the persistent schedule visits every query block exactly once, for any
       grid size;
     - Q, near and coarse tiles: every 16-byte load of every lane stays inside
@@ -15,6 +15,8 @@ buffers' sizes and against what the data layout says they must be:
       from one lane: it must be the same for all lanes), the near tiles cover
       exactly the near field, and every interaction-list slot maps to a row
       of its own coarse set (or is empty);
+  attend_group_kernel, bwd_query_mfma, bwd_coarse_mfma, bwd_key_mfma: the
+    library's own index functions, built for the host (group_emulation);
   coarsen1d_stream / coarsen2d_stream (coarsen.hip):
     - every step's rows and weight gathers stay inside their tensors and
       weight vectors;
@@ -29,6 +31,9 @@ A failed check raises AssertionError with the offending values.
 from __future__ import annotations
 
 import numpy as np
+
+import group_emulation
+import host_groups as hg
 
 KT = 64        # keys per tile
 ROWB = 128     # bytes per bf16 row of 64 channels
@@ -615,8 +620,8 @@ def check_pair_issue(P, grids=(1, 3, 8, 9, 100, 1024, 2048, 4096, 8192)):
 
 def small_blocks(P):
     """Blocks smaller than a wave (1D r < 64, 2D cells below 8 x 8), and any
-    head dim but 64: both dtypes take the register-staged kernel
-    (attend_kernel, row_source)."""
+    head dim but 64: plans that the fixed-shape stream does not take (bf16 runs
+    the groups or the register-staged kernel, fp32 the latter)."""
     return P["block"] < (64 if P["ndim"] == 1 else 8) or P["head_dim"] != 64
 
 
@@ -690,14 +695,26 @@ def check_generic_issue(P):
 
 
 def check_plan(P, grids=(1, 3, 8, 9, 100, 1024, 2048, 4096, 8192)):
-    """Every check that applies to the plan's forward pass."""
+    """Every check that applies to the plan's forward pass, on the kernels that
+    it may run (attend_route.hpp), and to the streamed backward of its blocks."""
     geom = "2d" if P["ndim"] == 2 else "1d"
-    if small_blocks(P):
-        return check_generic_issue(P), None
-    loads = check_attend_issue(P, geom, grids=grids)
-    if P.get("pair2d"):
-        loads = check_pair_issue(P, grids=grids)
     staged = None
     if P["nsets"] > 0 and P["dtype"] == 1 and P["depth"] > 0:
         staged = check_coarsen2d_stream(P) if geom == "2d" else check_coarsen1d_stream(P)
+    if P["dtype"] != 1:
+        return check_generic_issue(P), staged
+    kernels = hg.attend_kernels(hg.plan_values(P))
+    assert kernels, "no kernel takes the plan"
+    loads = 0
+    if kernels & hg.STAGED:
+        loads += check_generic_issue(P)
+    if kernels & hg.GROUPS:
+        loads += group_emulation.check_attend(P)
+    if kernels & hg.STREAM:
+        loads += check_attend_issue(P, geom, grids=grids)
+    assert bool(kernels & hg.PAIRS) == bool(P["pair2d"])
+    if kernels & hg.PAIRS:
+        loads += check_pair_issue(P, grids=grids)
+    if P["head_dim"] == 64 and P["block"] % (8 if geom == "2d" else 32) == 0:
+        group_emulation.check_backward(P)
     return loads, staged

@@ -15,7 +15,7 @@ def _plan(**kw):
     except F.FmaError as e:
         assert e.status in (F.FMA_ERR_UNSUPPORTED, F.FMA_ERR_SHAPE)
         return None
-    return hg.plan_values(op)
+    return hg.plan_values(F.fma_plan_params(op.handle))
 
 
 def _expected(kw):

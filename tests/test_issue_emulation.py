@@ -104,7 +104,7 @@ SHAPES = [
     # rank and size extremes: 64 coarse sets in 1D, 16 in 2D, a long sequence
     (1, False, "bf16", 1, 1, 4096, 64, 10, False), (1, True, "bf16", 2, 2, 1 << 20, 128, 4, False),
     (2, False, "bf16", 1, 1, 256, 8, 3, False),
-    # blocks smaller than a wave (the register-staged kernel)
+    # blocks smaller than a wave (the register-staged kernel; bf16 blocks of 32: the groups)
     (1, False, "bf16", 1, 2, 1024, 16, 1, False), (1, True, "bf16", 1, 2, 16 * 37, 16, 1, False),
     (1, False, "f32", 1, 2, 32 * 23, 32, 2, False), (1, True, "f32", 1, 1, 1024, 32, 1, True),
     (2, False, "bf16", 1, 2, 64, 4, 1, False), (2, False, "f32", 1, 1, 44, 4, 1, True),
@@ -139,7 +139,7 @@ def test_shape_addresses(case):
     emu.check_plan(P, grids=(1, 5, 8, 1024))
 
 
-# head dims 32 and 128 (the GPU tests' shapes): the register-staged kernel
+# head dims 32 and 128 (the GPU tests' shapes): the groups, or the register-staged kernel
 HEADDIM_SHAPES = [
     (1, False, "bf16", 2, 2, 1024, 64, 1, False, 32), (1, True, "bf16", 1, 2, 4096, 128, 1, False, 128),
     (1, False, "f32", 1, 2, 1024, 64, 1, False, 128), (1, True, "f32", 1, 2, 16 * 37, 16, 1, False, 32),
