@@ -59,6 +59,11 @@
  *     kept per thread for fma_last_error().  Launch failures are reported
  *     as FMA_ERR_HIP.
  *   - Determinism: no atomics; repeated calls give bitwise identical output.
+ *     Which attention kernel runs a plan can depend on how many CUs its B * H
+ *     slices fill (fp32; bf16 at d = 64: blocks of 256, bidirectional blocks of
+ *     128 and 192), and the kernels differ in rounding: the same (b, h) slice
+ *     may come out different in its last bits in calls of another B * H, or
+ *     on a GPU with another number of CUs.
  *   - Thread safety: a plan is immutable after fma_plan() and may be used
  *     from several threads / streams at once with distinct workspaces.
  */
@@ -105,16 +110,16 @@ typedef struct {
     int32_t heads;            /* H >= 0 */
     int64_t seq_len;          /* n >= 0; 2D: n == H * side, token x * W + y in row x, column y */
     int32_t side;             /* 2D map width W (columns, > 0); H = seq_len / W; ignored (0) in 1D */
-    int32_t head_dim;         /* d: 32, 64 or 128 (the matrix-core fused attention and streaming
-                                 coarsening are built for 64; 32 and 128 run on the register-
-                                 staged attention and the chunk / tile coarsening; the backward
-                                 takes 64 only) */
+    int32_t head_dim;         /* d: 32, 64 or 128 (the bf16 streaming coarsening, FMA-linear's
+                                 matrix-core kernels and the backward are built for 64; bf16 plans
+                                 at 32 and 128 run the attention on groups of 128 queries, or the
+                                 register-staged one, and the chunk / tile coarsening) */
     int32_t block;            /* r: 1D block length / 2D cell side; r | n (2D: r | W and r | H) */
     int32_t num_levels;       /* L = ceil(log2(n/r)) (2D: max(H, W)/r, the longer side); -1 derives it */
     int32_t causal;           /* 0 or 1; 1D only */
     int32_t dtype;            /* fma_dtype_t */
     int32_t weights_per_head; /* 1: weights are [H][wlen]; 0: one [wlen] set for all heads */
-    float softmax_scale;      /* tau; 0 selects 1/sqrt(head_dim) */
+    float softmax_scale;      /* tau, any finite value; 0 selects 1/sqrt(head_dim) */
     int32_t rank;             /* p >= 1 basis vectors per level (Sec. 3); 0 selects 1.  A
                                  struct_size that ends before this field means p = 1 */
     int32_t norm;             /* fma_norm_t; a struct_size that ends before `rank` means joint */
@@ -205,7 +210,7 @@ fma_status_t fma_dense_reference(fma_plan_t plan, const void *q, const void *k, 
 
 /* Test export: the scalar launch parameters the plan hands its kernels, for
  * host-side checks of the kernels' address arithmetic (no device access).
- * Writes *count = 40 + 6 * sets int64 values to out (FMA_ERR_WORKSPACE,
+ * Writes *count = 41 + 6 * sets int64 values to out (FMA_ERR_WORKSPACE,
  * with *count set, if capacity is smaller), in this order:
  *   n, side (W), block, cells along x (H/r; 1D: blocks), queries per query tile,
  *   query tiles per slice, slices (B*H), coarse rows per slice R, causal,
@@ -218,9 +223,10 @@ fma_status_t fma_dense_reference(fma_plan_t plan, const void *q, const void *k, 
  *   depth of the bf16 streaming kernels (0: fp32 kernels), LDS bytes per
  *   streaming wave, LDS bytes per coarsening workgroup;
  *   workspace: partial-sum offset, coarse bytes, total bytes;
- *   FMA-linear, weight sets (heads or 1), dtype, whether the bf16 fused
- *   attention takes the 2D map's cells in horizontal pairs;
- *   2D: map height H, cells along y (W/r), tiles along x (0 in 1D);
+ *   FMA-linear, weight sets (heads or 1), dtype, whether the bf16 stream
+ *   takes the map's cells in horizontal pairs (per-level plans of rank 2 and
+ *   more);
+ *   2D: map height H, cells along y (W/r), tiles along x (0 in 1D); head dim;
  * then per coarse set: first coarse row, groups (2D: rows of squares),
  * 2D columns of squares (1D: 1), group size, weight offset, level. */
 fma_status_t fma_plan_params(fma_plan_t plan, int64_t *out, int32_t capacity, int32_t *count);

@@ -630,7 +630,10 @@ __global__ __launch_bounds__(64 * NW * KS) void attend_kernel(AttnArgs a)
 // LDS at d = 64).  Blocks of 64, whole blocks -> split: 32 pieces 39.5 -> 18.6 us,
 // 256 pieces 39.6 -> 19.3 (causal 31.1 -> 19.0), blocks of 128, 64 pieces 59.4 ->
 // 29.1; past the line 512 pieces 38.4 -> 35.4 but causal 30.1 -> 35.3, 1024 pieces
-// 42.5 -> 67.9.
+// 42.5 -> 67.9.  At d = 32 (71 KB, two workgroups a CU) the split gains at the
+// line as well (256 pieces, blocks of 64 26.0 -> 12.1 us, blocks of 256 92.8 ->
+// 33.2, 8 x 8 cells 48.7 -> 23.3) and up to 512 pieces (26.1 -> 16.4, causal 20.7
+// -> 16.1); 1024 pieces 34.9 -> 30.1, causal 27.3 -> 29.2.
 constexpr unsigned kSplitPieces = 256;
 
 template <bool BF16, int GEOM, bool LIN, int D, bool WIDE>

@@ -4,11 +4,14 @@
 // (attend_route.hpp tells where it is taken).
 //
 // What bounds it: at 1D 65536 x 128, 32 slices, its loads and stores alone take
-// 181 us (1.08 GB at 6 TB/s) and its arithmetic alone 250-295 us, the sum of
-// the matrix and vector instructions' cycles per 32 x 32 piece (256 + ~350);
-// two, three or four waves per SIMD, and two pieces at a time, measure the
-// same, so the vector work per piece (16 exponentials, 16
-// shifts by m, 8 conversions, 8 pair sums) is what is left.
+// 181 us (1.08 GB at 6 TB/s) and its arithmetic alone 250-295 us (matrix and
+// vector instructions of a 32 x 32 piece, 256 + ~350 cycles); two, three or
+// four waves per SIMD, and two pieces at a time, measure the same.  Between
+// that and the kernel's time lies the start of every group, ~5 us of set
+// tables, list table, queries and first tile before 13.5 us of loop, which only
+// the CU's other workgroups hide: the dense reference runs the same arithmetic
+// per piece at 856 TFLOP/s (16 384 keys a query), this kernel a 128 x 128 map
+// at 573.
 //
 // Four waves of 32 queries share the group's near window and list rows, which
 // stream through two LDS stages of at most 8 KB per tensor (32 rows at d =

@@ -59,9 +59,13 @@
 // over those rows takes them as the B operand and reads the A operand from a
 // transposed LDS copy in the same row order.
 //
-// Every global load and store is checked against the size of its buffer
-// (elements, from the argument block); out-of-range loads read 0 and
-// out-of-range stores are dropped.
+// In this file every global load and store is checked against the size of its
+// buffer (elements, from the argument block); out-of-range loads read 0 and
+// out-of-range stores are dropped.  The streamed kernels of backward_mfma.hip
+// check only the key pass's K and V rows and the sums of partial rows: their
+// addresses come from row_groups.hpp, whose functions also compile for the host
+// and are checked there against each plan's buffers, and launch_query checks
+// the partials' space.
 #include "bwd_tiles.hpp"
 #include "fma_device.hpp"
 #include "fma_kernels.hpp"

@@ -1,6 +1,6 @@
 // backward_mfma.hip -- the bf16 backward on streams of direct-to-LDS tiles
-// (see backward.hip for the method and bwd_tiles.hpp for the groups of rows
-// and their windows).
+// (see backward.hip for the method and row_groups.hpp for the groups of rows,
+// their windows and lists).
 #include "bwd_tiles.hpp"
 
 namespace fma_dev {

@@ -1,4 +1,4 @@
-"""CPU restatement of the row groups of the bf16 backward (bwd_tiles.hpp):
+"""CPU restatement of the row groups of the bf16 backward (row_groups.hpp):
 which tokens every workgroup loads and which of them each wave takes, against
 the definition of the near field, for every block size the groups accept."""
 import pytest
