@@ -32,7 +32,7 @@ inline bool group_fits(const AttnArgs &a, bool two_d)
 //
 // Groups are the faster kernel for head dims 32 and 128 and blocks of 32
 // against the register-staged one (d = 128 causal 7808 x 128, 64 slices: 581 ->
-// 153 us; blocks of 32, 64 slices of 4000: 207 -> 41 us), and at d = 64 against
+// 149 us; blocks of 32, 64 slices of 4000: 207 -> 42 us), and at d = 64 against
 // the stream for every 2D map (128 x 128 at 32 slices 163 -> 141 us, 16 x 16
 // cells 418 -> 322, 120 x 168 per level 272 -> 233), 1D blocks of 64 (48 slices
 // of 16384: 150 -> 111 us, causal 128 -> 89), causal blocks of 192 (169 -> 126)
